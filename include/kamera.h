@@ -27,8 +27,8 @@
  * Conventions shared by every entry point
  *   - Every tensor pointer is a DEVICE pointer owned by the caller.  The
  *     library never allocates, frees or synchronises; a call enqueues its
- *     kernel (kamera_form_patch: two, one after the other) on `stream` (a
- *     hipStream_t; NULL = the default stream) and returns.  Results are
+ *     kernel (kamera_form_patch: two or three, one after the other) on
+ *     `stream` (a hipStream_t; NULL = the default stream) and returns.  Results are
  *     visible to later work on that stream.
  *   - KV rows are bf16.  Strides are in ELEMENTS (bf16) unless named _bytes;
  *     the innermost (column) stride is always 1.  Row starts must be 16-byte
@@ -353,12 +353,14 @@ typedef struct {
  *   sweeps = 0 (default): Householder reduction to tridiagonal form,
  *     multisection on Sturm counts for the eigenvalues, twisted
  *     factorisation for their eigenvectors (close eigenvalues, within 1e-3 of
- *     the spectral norm, reorthogonalised), back-transformation;
+ *     the spectral norm, reorthogonalised), back-transformation; a unit whose vectors fail its
+ *     checks (exactly multiple eigenvalues) is formed again by block Jacobi
+ *     in a launch of its own;
  *   sweeps > 0: block cyclic Jacobi, at most `sweeps` sweeps, stopping once
  *     the off-diagonal mass is negligible (12 reach the fp32 floor here).
  * Either way singular vectors are accurate to ~1e-5 relative where the
  * spectrum has a gap at m.  W = V_m^T (bf16) is written first; U = Delta W^T
- * is then formed from that stored W in a second launch on the same stream
+ * is then formed from that stored W in a later launch on the same stream
  * (Delta enters as a two-part bf16 split, ~2^-16 relative), so that U W is
  * the projection onto exactly the kept W.
  * Orbit patch (Sec. 5, reorder): with n_orbit = K >= 2 the deficits of K

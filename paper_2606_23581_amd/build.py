@@ -36,7 +36,7 @@ def _run(cmd, verbose):
     return res
 
 
-DEVICE_SOURCES = ("kamera_kernels.hip", "kamera_rows.hip", "kamera_patch.hip")
+DEVICE_SOURCES = ("kamera_kernels.hip", "kamera_rows.hip", "kamera_patch.hip", "kamera_tridiag.hip")
 
 
 def build(verbose: bool = False, save_temps: bool = False) -> str:

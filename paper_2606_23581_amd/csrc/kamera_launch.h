@@ -185,6 +185,8 @@ struct FormParams {
   float inv_orbit;                  // 1 / n_orbit
   int32_t w_vec;                    // W rows 16-byte aligned: 8 entries per load
   int32_t u_pair;                   // U rows 4-byte aligned: 2 ranks per store
+  int32_t z_groups;                 // tridiagonal solver: LDS groups of 32 columns, set at launch
+  int32_t pad_;
 };
 
 size_t form_lds_bytes(int dim, int m);
@@ -208,6 +210,7 @@ inline hipError_t ensure_lds_limit(const void* fn, int bytes, std::atomic<bool> 
 hipError_t launch_rehydrate(const RehydrateParams& p, hipStream_t s);
 hipError_t launch_rehydrate_rows(const RehydrateParams& p, hipStream_t s);
 hipError_t launch_form_patch(const FormParams& p, hipStream_t s);
+hipError_t launch_form_tridiag(const FormParams& p, hipStream_t s);
 hipError_t launch_shift(const ShiftParams& p, hipStream_t s);
 hipError_t launch_scatter(const ScatterParams& p, hipStream_t s);
 

@@ -624,6 +624,38 @@ def test_form_patch_matches_svd(device, n, d, m):
     assert (capped == 1).all()
 
 
+@pytest.mark.parametrize("units,n,d,m,w_odd", [(8, 33, 128, 32, False), (8, 129, 128, 33, True),
+                                               (520, 48, 128, 40, False), (8, 200, 100, 65, True),
+                                               (8, 47, 68, 34, False), (8, 16, 8, 8, True)])
+def test_form_patch_block_edges(device, units, n, d, m, w_odd):
+    """The tridiagonal solver where its layout changes: column counts around its
+    32-wide blocks, token counts around its 16-row stages, ranks around one and
+    two groups of 32 vectors, launches of more than two units per CU (one lane
+    per vector instead of two), and W rows that are not 16-byte aligned."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch block edges units {units} n{n} d{d} m{m}", flush=True)
+    rng = np.random.default_rng(n * 1000 + d + m)
+    delta = np.empty((1, 1, units, n, d), np.float32)
+    for u in range(units):
+        r = min(m, n, d)
+        A = np.linalg.qr(rng.standard_normal((n, r)))[0]
+        B = np.linalg.qr(rng.standard_normal((d, r)))[0]
+        delta[0, 0, u] = (A * np.linspace(10.0, 2.0, r)) @ B.T + 0.01 * rng.standard_normal((n, d))
+    U = torch.zeros((1, 1, units, n, m), dtype=torch.bfloat16, device=device)
+    W = torch.zeros((1, 1, units, m, d + 1 if w_odd else d), dtype=torch.bfloat16, device=device)
+    sigma = torch.zeros((1, 1, units, m), dtype=torch.float32, device=device)
+    done = torch.full((1, 1, units), -1, dtype=torch.int32, device=device)
+    km.form_patch(torch.from_numpy(delta).to(device), U, W[..., :d], sigma=sigma, sweeps_done=done)
+    torch.cuda.synchronize()
+    assert (done == 0).all(), done.cpu().numpy()
+    Ub, Wb, sg = bits(U), bits(W), sigma.cpu().numpy()
+    assert not w_odd or (Wb[..., d] == 0).all()
+    for u in list(range(8)) + list(range(units - 8, units)):
+        _check_patch(delta[0, 0, u], Ub[0, 0, u], Wb[0, 0, u][:, :d], sg[0, 0, u], m, (u,))
+
+
 @pytest.mark.parametrize("sweeps", [0, 12])
 def test_form_patch_degenerate_spectra(device, sweeps):
     """Spectra where the eigensolvers meet multiple or zero eigenvalues:
