@@ -124,6 +124,7 @@ void fill_place(kamera::Placement& pl, int32_t n_tokens, const int32_t* chunk_to
   pl.page_size = paged ? page_size : 1;
   pl.n_pool_pages = n_pool_pages;
   pl.status = status;
+  pl.fd_page = kamera::make_fast_div((uint32_t)pl.page_size);
 }
 
 bool strides_ok(const int64_t* s, int n) {
@@ -578,15 +579,20 @@ static int build_shift(const kamera_shift_args* a, kamera::ShiftParams& P, bool&
   P.n_layers = a->n_layers;
   P.n_heads = a->n_heads;
   P.vec_per_row = r.pairing == KAMERA_PAIR_NEOX ? r.rope_dim / 16 : r.rope_dim / 8;
-  // about 512 rows per task, at least 2048 tasks when the call is large enough
+  // about 512 rows per task; a smaller call takes smaller tasks until it has
+  // 2048 of them or a thread of each is left with one row
+  const int rows_per_pass = kamera::kThreads / P.vec_per_row;
   int tb = 16;
   while (tb < 1024 && (int64_t)tb * a->n_heads < 512) tb *= 2;
-  while (tb > 16 && (int64_t)a->n_chunks * a->n_layers * ceil_div(a->n_tokens, tb) < 2048) tb /= 2;
+  while (tb > 1 && (int64_t)tb * a->n_heads > rows_per_pass &&
+         (int64_t)a->n_chunks * a->n_layers * ceil_div(a->n_tokens, tb) < 2048)
+    tb /= 2;
   P.token_block = tb;
   P.n_tblk = (int32_t)ceil_div(a->n_tokens, tb);
   P.n_tasks = (int64_t)a->n_chunks * a->n_layers * P.n_tblk;
   P.fd_tblk = kamera::make_fast_div((uint32_t)std::max(1, P.n_tblk));
   P.fd_layers = kamera::make_fast_div((uint32_t)std::max(1, a->n_layers));
+  P.fd_heads = kamera::make_fast_div((uint32_t)std::max(1, a->n_heads));
   rc = pick_grid(P.n_tasks, P.per_xcd, who);
   if (rc) return rc;
   launch = true;
@@ -659,6 +665,7 @@ static int build_scatter(const kamera_scatter_args* a, kamera::ScatterParams& P,
   P.n_tasks = (int64_t)a->n_chunks * a->n_layers * P.n_tblk;
   P.fd_tblk = kamera::make_fast_div((uint32_t)std::max(1, P.n_tblk));
   P.fd_layers = kamera::make_fast_div((uint32_t)std::max(1, a->n_layers));
+  P.fd_vpr = kamera::make_fast_div((uint32_t)std::min<int64_t>(P.row_vecs, 1 << 30));
   rc = pick_grid(P.n_tasks, P.per_xcd, who);
   if (rc) return rc;
   launch = true;

@@ -72,6 +72,19 @@ __device__ __forceinline__ int64_t page_slot(const Placement& pl, int c, int i) 
   return (int64_t)page * pl.page_size + i % pl.page_size;
 }
 
+// The slots of tokens [t_begin, t_end) (at most kMaxTokenBlock) into s_slot,
+// by all kThreads threads of a workgroup; -1 as in page_slot.
+__device__ __forceinline__ void stage_slots(const Placement& pl, int c, int t_begin, int t_end, int64_t* s_slot) {
+  for (int t = threadIdx.x; t < t_end - t_begin; t += kThreads) {
+    const uint32_t i = (uint32_t)(t_begin + t), k = fast_div(i, pl.fd_page);
+    const int page = pl.page_table[(int64_t)c * pl.pt_stride + k];
+    int64_t slot = -1;
+    if (page >= 0 && page < pl.n_pool_pages) slot = (int64_t)page * pl.page_size + (i - k * (uint32_t)pl.page_size);
+    else if (pl.status != nullptr) atomicOr(pl.status, KAMERA_STATUS_BAD_PAGE);
+    s_slot[t] = slot;
+  }
+}
+
 // The launch parameters are read in place from the kernel-argument segment.
 // Taking the address of a by-value kernel parameter (its arrays are indexed
 // with run-time values) would make the compiler copy the whole struct into

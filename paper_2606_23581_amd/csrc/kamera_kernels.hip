@@ -30,6 +30,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kamera_device.h"
 
 namespace kamera {
@@ -597,8 +599,18 @@ hipError_t launch_rehydrate(const RehydrateParams& p, hipStream_t s) {
 
 constexpr int kShiftUnroll = 4;
 
+// A thread owns one 16-byte vector of the band (NeoX: and its partner vector)
+// and streams rows.  Bound by HBM on large calls; a small one is a chain of
+// dependent loads (arguments, row base or page, rows), so the first rows are in
+// flight while the angles are formed, and the host gives each thread a single
+// row until there are 2048 workgroups (one layer of 256 tokens x 8 heads: 9.4
+// us in 16 workgroups of four rows a thread, angles first; 4.3 us this way).
+// Rows are found by a multiply-high division and slots in LDS: 802 -> 762 us on
+// 15 x 512 tokens x 32 layers x 32 heads.
+template <bool NEOX, bool PAGED>
 __global__ __launch_bounds__(kThreads) void shift_kernel(const ShiftParams /*by value, read in place*/) {
   const ShiftParams& P = kernel_params<ShiftParams>();
+  __shared__ int64_t s_slot[PAGED ? kMaxTokenBlock : 1];
   const int64_t task = xcd_task(P.per_xcd);
   if (task >= P.n_tasks) return;
   const uint32_t tk = (uint32_t)task, q = fast_div(tk, P.fd_tblk), c32 = fast_div(q, P.fd_layers);
@@ -609,66 +621,63 @@ __global__ __launch_bounds__(kThreads) void shift_kernel(const ShiftParams /*by 
   const int t_begin = tb * P.token_block;
   if (t_begin >= n_c) return;
   const int t_end = min(t_begin + P.token_block, n_c);
+  if constexpr (PAGED) {
+    stage_slots(P.place, c, t_begin, t_end, s_slot);
+    __syncthreads();
+  }
 
   const int vpr = P.vec_per_row;
   const int rpp = kThreads / vpr;                 // rows per pass
-  if ((int)threadIdx.x >= rpp * vpr) return;       // no barrier in this kernel
+  if ((int)threadIdx.x >= rpp * vpr) return;       // no barrier from here on
   const int v = threadIdx.x % vpr;
   const int r0 = threadIdx.x / vpr;
-  const bool neox = P.rope.pairing == 0;
   const int half = P.rope.rope_dim / 2;
-
-  // the angles depend only on (chunk delta, pair): computed once per thread
-  const double d3[3] = {(double)P.delta[3 * c], (double)P.delta[3 * c + 1], (double)P.delta[3 * c + 2]};
-  float cs[8], sn[8];
-  const int npair = neox ? 8 : 4;
-  const int j0 = neox ? 8 * v : 4 * v;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    if (e < npair) {
-      const int j = j0 + e;
-      sincos_rev(d3[P.rope.coord[j]], P.rope.rev_freq[j], sn[e], cs[e]);
-    } else {
-      sn[e] = 0.f;
-      cs[e] = 1.f;
-    }
-  }
   const int xcol = P.rope.rope_offset + 8 * v;
   const int ycol = xcol + half;                   // NeoX partner chunk
 
-  const int H = P.n_heads;
-  const int rows = (t_end - t_begin) * H;
-  for (int base = r0; base < rows; base += kShiftUnroll * rpp) {
-    u32x4 xv[kShiftUnroll], yv[kShiftUnroll];
-    uint16_t* rp[kShiftUnroll];
+  const uint32_t H = (uint32_t)P.n_heads;
+  const int rows = (t_end - t_begin) * (int)H;
+  const int64_t dense0 = PAGED ? 0
+                               : (int64_t)c * P.k_s[0] +
+                                     ((int64_t)(P.place.row_base ? P.place.row_base[c] : 0) + t_begin) * P.k_s[2];
+  uint16_t* const kl = P.k + (int64_t)l * P.k_s[1] + dense0;
+  u32x4 xv[kShiftUnroll], yv[kShiftUnroll];
+  uint16_t* rp[kShiftUnroll];
+  auto load = [&](int base) {
 #pragma unroll
     for (int u = 0; u < kShiftUnroll; ++u) {
       const int row = base + u * rpp;
       rp[u] = nullptr;
       if (row < rows) {
-        const int i = t_begin + row / H;
-        const int h = row % H;
-        int64_t off;
-        if (P.place.paged) {
-          const int64_t slot = page_slot(P.place, c, i);
-          off = slot < 0 ? -1 : (int64_t)l * P.k_s[1] + slot * P.k_s[2] + (int64_t)h * P.k_s[3];
-        } else {
-          const int rb = P.place.row_base ? P.place.row_base[c] : 0;
-          off = (int64_t)c * P.k_s[0] + (int64_t)l * P.k_s[1] + (int64_t)(rb + i) * P.k_s[2] +
-                (int64_t)h * P.k_s[3];
-        }
-        if (off >= 0) {
-          rp[u] = P.k + off;
+        const uint32_t i = fast_div((uint32_t)row, P.fd_heads), h = (uint32_t)row - i * H;
+        const int64_t slot = PAGED ? s_slot[PAGED ? i : 0] : (int64_t)i;
+        if (!PAGED || slot >= 0) {
+          rp[u] = kl + slot * P.k_s[2] + (int64_t)h * P.k_s[3];
           xv[u] = ld16(rp[u] + xcol);
-          if (neox) yv[u] = ld16(rp[u] + ycol);
+          if (NEOX) yv[u] = ld16(rp[u] + ycol);
         }
       }
     }
+  };
+  load(r0);
+
+  // the angles depend only on (chunk delta, pair): computed once per thread
+  constexpr int kPairs = NEOX ? 8 : 4;
+  float cs[kPairs], sn[kPairs];
+  {
+    const int j0 = kPairs * v;
+    const double d3[3] = {(double)P.delta[3 * c], (double)P.delta[3 * c + 1], (double)P.delta[3 * c + 2]};
+#pragma unroll
+    for (int e = 0; e < kPairs; ++e) {
+      const int sc = P.rope.coord[j0 + e];
+      sincos_rev(sc == 0 ? d3[0] : (sc == 1 ? d3[1] : d3[2]), P.rope.rev_freq[j0 + e], sn[e], cs[e]);
+    }
+  }
+  for (int base = r0; base < rows;) {
 #pragma unroll
     for (int u = 0; u < kShiftUnroll; ++u) {
       if (rp[u] == nullptr) continue;
-      if (neox) {
-        u32x4 xo, yo;
+      if constexpr (NEOX) {
         uint32_t xw[4], yw[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -678,10 +687,8 @@ __global__ __launch_bounds__(kThreads) void shift_kernel(const ShiftParams /*by 
           xw[k] = pack_bf16x2(x0 * cs[e0] - y0 * sn[e0], x1 * cs[e1] - y1 * sn[e1]);
           yw[k] = pack_bf16x2(x0 * sn[e0] + y0 * cs[e0], x1 * sn[e1] + y1 * cs[e1]);
         }
-        xo = u32x4{xw[0], xw[1], xw[2], xw[3]};
-        yo = u32x4{yw[0], yw[1], yw[2], yw[3]};
-        st16(rp[u] + xcol, xo);
-        st16(rp[u] + ycol, yo);
+        st16(rp[u] + xcol, u32x4{xw[0], xw[1], xw[2], xw[3]});
+        st16(rp[u] + ycol, u32x4{yw[0], yw[1], yw[2], yw[3]});
       } else {
         uint32_t ow[4];
 #pragma unroll
@@ -693,12 +700,20 @@ __global__ __launch_bounds__(kThreads) void shift_kernel(const ShiftParams /*by 
         st16(rp[u] + xcol, u32x4{ow[0], ow[1], ow[2], ow[3]});
       }
     }
+    base += kShiftUnroll * rpp;
+    if (base < rows) load(base);
   }
 }
 
 hipError_t launch_shift(const ShiftParams& p, hipStream_t s) {
-  const int64_t grid = (int64_t)p.per_xcd * 8;
-  hipLaunchKernelGGL(shift_kernel, dim3((uint32_t)grid), dim3(kThreads), 0, s, p);
+  const dim3 grid((uint32_t)((int64_t)p.per_xcd * 8)), block(kThreads);
+  if (p.rope.pairing == 0) {
+    if (p.place.paged) hipLaunchKernelGGL((shift_kernel<true, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((shift_kernel<true, false>), grid, block, 0, s, p);
+  } else {
+    if (p.place.paged) hipLaunchKernelGGL((shift_kernel<false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((shift_kernel<false, false>), grid, block, 0, s, p);
+  }
   return hipGetLastError();
 }
 
@@ -708,8 +723,15 @@ hipError_t launch_shift(const ShiftParams& p, hipStream_t s) {
 
 constexpr int kScatterUnroll = 4;
 
+// Bound by HBM once the index work is small: the slots of the block's tokens
+// are looked up once, into LDS, and a vector's row comes from a multiply-high
+// division.  (With a 64-bit run-time division and a table lookup per 16-byte
+// vector the vector ALU was the limit: 4.15 TB/s on 8 x 32 x 1024 rows of 2
+// KiB, against 5.1.)  WIDE: rows of 2^26 vectors or more, whose indices need 64 bits.
+template <bool GATHER, bool WIDE>
 __global__ __launch_bounds__(kThreads) void scatter_kernel(const ScatterParams /*by value, read in place*/) {
   const ScatterParams& P = kernel_params<ScatterParams>();
+  __shared__ int64_t s_slot[kMaxTokenBlock];
   const int64_t task = xcd_task(P.per_xcd);
   if (task >= P.n_tasks) return;
   const uint32_t tk = (uint32_t)task, q = fast_div(tk, P.fd_tblk), c32 = fast_div(q, P.fd_layers);
@@ -720,28 +742,31 @@ __global__ __launch_bounds__(kThreads) void scatter_kernel(const ScatterParams /
   const int t_begin = tb * P.token_block;
   if (t_begin >= n_c) return;
   const int t_end = min(t_begin + P.token_block, n_c);
-  const int64_t vpr = P.row_vecs;
-  const int64_t total = (int64_t)(t_end - t_begin) * vpr;
-  uint8_t* rbase = P.rows + (int64_t)c * P.rows_s[0] + (int64_t)l * P.rows_s[1];
-  uint8_t* pbase = P.pool + (int64_t)l * P.pool_s[0];
-  const bool gather = P.gather != 0;
-  for (int64_t base = threadIdx.x; base < total; base += kScatterUnroll * kThreads) {
+  stage_slots(P.place, c, t_begin, t_end, s_slot);
+  __syncthreads();
+  typedef typename std::conditional<WIDE, int64_t, uint32_t>::type idx_t;
+  const idx_t vpr = (idx_t)P.row_vecs;
+  const idx_t total = (idx_t)(t_end - t_begin) * vpr;
+  uint8_t* const rbase = P.rows + (int64_t)c * P.rows_s[0] + (int64_t)l * P.rows_s[1] + (int64_t)t_begin * P.rows_s[2];
+  uint8_t* const pbase = P.pool + (int64_t)l * P.pool_s[0];
+  for (idx_t base = threadIdx.x; base < total; base += kScatterUnroll * kThreads) {
     u32x4 v[kScatterUnroll];
     uint8_t* dp[kScatterUnroll];
 #pragma unroll
     for (int u = 0; u < kScatterUnroll; ++u) {
-      const int64_t idx = base + (int64_t)u * kThreads;
+      const idx_t idx = base + (idx_t)(u * kThreads);
       dp[u] = nullptr;
       if (idx < total) {
-        const int i = t_begin + (int)(idx / vpr);
-        const int64_t vec = idx % vpr;
-        const int64_t slot = page_slot(P.place, c, i);
+        idx_t i;
+        if constexpr (WIDE) i = idx / vpr;
+        else i = fast_div(idx, P.fd_vpr);
+        const int64_t at = 16 * (int64_t)(idx - i * vpr);
+        const int64_t slot = s_slot[i];
         if (slot >= 0) {
-          uint8_t* dense = rbase + (int64_t)i * P.rows_s[2] + 16 * vec;
-          uint8_t* paged = pbase + slot * P.pool_s[1] + 16 * vec;
-          const uint8_t* sp = gather ? paged : dense;
-          dp[u] = gather ? dense : paged;
-          v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(sp));
+          uint8_t* const dense = rbase + (int64_t)i * P.rows_s[2] + at;
+          uint8_t* const paged = pbase + slot * P.pool_s[1] + at;
+          dp[u] = GATHER ? dense : paged;
+          v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(GATHER ? paged : dense));
         }
       }
     }
@@ -752,8 +777,15 @@ __global__ __launch_bounds__(kThreads) void scatter_kernel(const ScatterParams /
 }
 
 hipError_t launch_scatter(const ScatterParams& p, hipStream_t s) {
-  const int64_t grid = (int64_t)p.per_xcd * 8;
-  hipLaunchKernelGGL(scatter_kernel, dim3((uint32_t)grid), dim3(kThreads), 0, s, p);
+  const dim3 grid((uint32_t)((int64_t)p.per_xcd * 8)), block(kThreads);
+  const bool wide = p.row_vecs >= (int64_t)1 << 26;
+  if (p.gather) {
+    if (wide) hipLaunchKernelGGL((scatter_kernel<true, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((scatter_kernel<true, false>), grid, block, 0, s, p);
+  } else {
+    if (wide) hipLaunchKernelGGL((scatter_kernel<false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((scatter_kernel<false, false>), grid, block, 0, s, p);
+  }
   return hipGetLastError();
 }
 

@@ -12,6 +12,7 @@ namespace kamera {
 
 constexpr int kThreads = 256;        // 4 wave64 per workgroup
 constexpr int kTileTokens = 16;      // tokens per wave tile (MFMA N dimension)
+constexpr int kMaxTokenBlock = 1024; // tokens per task of the per-head, shift and scatter kernels
 constexpr int kMaxBlocks = 36;       // column blocks per row (head_dim <= 4096)
 constexpr int kMaxPairs = 64;        // rotated pairs (rope_dim <= 128)
 constexpr int kRgMaxHeads = 8;       // heads of a row taken by one row-group workgroup
@@ -99,6 +100,7 @@ struct Placement {                   // where token i of chunk c lands / sits
   int32_t n_pool_pages;
   int32_t pad_;
   uint32_t* status;
+  FastDiv fd_page;                   // division by page_size
 };
 
 struct RehydrateParams {
@@ -144,6 +146,7 @@ struct ShiftParams {
   int32_t pad_;
   int64_t n_tasks;
   FastDiv fd_tblk, fd_layers;        // task decode
+  FastDiv fd_heads;                  // row -> (token, head)
 };
 
 struct ScatterParams {
@@ -160,6 +163,7 @@ struct ScatterParams {
   int32_t gather;                    // 1: pool -> dense rows
   int64_t n_tasks;
   FastDiv fd_tblk, fd_layers;        // task decode
+  FastDiv fd_vpr;                    // vector -> row (row_vecs < 2^26)
 };
 
 constexpr int kFormMaxDim = 128;     // patch forming: columns of Delta

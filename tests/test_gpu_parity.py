@@ -430,6 +430,42 @@ def test_shift_matches_oracle(device, name):
     assert int(status.cpu()[0]) == 0
 
 
+@pytest.mark.parametrize("pairing", ["neox", "interleaved"])
+@pytest.mark.parametrize("H,n,P,rope_dim", [(1, 7, 0, 128), (3, 50, 24, 64), (5, 129, 16, 128), (33, 40, 0, 16)])
+def test_shift_small_tasks(device, pairing, H, n, P, rope_dim):
+    """Shift where a thread has one row and the last task is partly empty: odd
+    head counts, ragged chunks, dense rows and pages of 24 and 16."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] shift small {pairing} H{H} n{n} P{P} rope{rope_dim}", flush=True)
+    rng = np.random.default_rng(H * 10 + n)
+    C, L, D = 2, 2, 128
+    rs = km.RopeSpec(theta=1e4, rope_dim=rope_dim, pairing=pairing)
+    delta = np.repeat(rng.integers(-3000, 3000, size=(C, 1)), 3, axis=1).astype(np.int32)
+    n_c = np.array([n, n - 3], np.int32)
+    pages = (n + P - 1) // P if P else 0
+    npp = C * pages + 1
+    Kb = synth.randn_bf16_numpy((L, npp * P if P else C * n, H, D), 1.0, rng)
+    kt = dev(Kb, device)
+    pt = rng.permutation(npp)[: C * pages].reshape(C, pages).astype(np.int32)
+    kw = dict(page_table=dev_i32(pt, device), page_size=P, n_pool_pages=npp) if P else \
+        dict(row_base=dev_i32(n * np.arange(C), device))
+    km.shift(kt, dev_i32(delta, device), rope=rs, n_chunks=C, n_tokens=n, chunk_tokens=dev_i32(n_c, device), **kw)
+    torch.cuda.synchronize()
+    out = bits(kt)
+    touched = np.zeros(out.shape[1], bool)
+    for c in range(C):
+        i = np.arange(n_c[c])
+        at = pt[c][i // P] * P + i % P if P else n * c + i
+        touched[at] = True
+        for l in range(L):
+            for h in range(H):
+                want = ref.shift_k(ref.bf16_to_f64(Kb[l, at, h]), oracle_rope(rs), delta[c])
+                assert_close(out[l, at, h], want, f"c{c} l{l} h{h}")
+    assert np.array_equal(out[:, ~touched], Kb[:, ~touched])
+
+
 def test_shift_round_trip(device):
     """Shift by delta then -delta returns the keys within two bf16 roundings."""
     import paper_2606_23581_amd as km
@@ -477,6 +513,39 @@ def test_scatter_is_bit_exact(device):
             want[l] = ref.scatter_paged(src[c, l, : n_c[c]], pt[c], P, want[l])
     assert np.array_equal(out, want)
     assert int(status.cpu()[0]) == 0
+
+
+@pytest.mark.parametrize("C,L,n,vecs,P", [(3, 2, 45, 7, 24), (2, 3, 70, 72, 1), (64, 32, 1030, 1, 16),
+                                          (2, 1, 33, 130, 64), (1, 1, 1, 1, 5)])
+def test_scatter_gather_row_widths(device, C, L, n, vecs, P):
+    """Scatter and gather with rows of odd numbers of 16-byte vectors, page sizes
+    that are not powers of two, ragged chunks and token blocks of 16 to 1024
+    tokens: every byte of the pool, then every byte of the rows read back."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] scatter/gather C{C} L{L} n{n} vecs{vecs} P{P}", flush=True)
+    rng = np.random.default_rng(C * 100 + vecs)
+    src = rng.integers(0, 1 << 16, size=(C, L, n, 8 * vecs)).astype(np.uint16)
+    pages = (n + P - 1) // P
+    npp = C * pages + 3
+    pt = rng.permutation(npp)[: C * pages].reshape(C, pages).astype(np.int32)
+    n_c = rng.integers(0, n + 1, size=C).astype(np.int32)
+    n_c[0] = n
+    pool = dev(np.full((L, npp * P, 8 * vecs), SENTINEL, np.uint16), device)
+    kw = dict(page_size=P, n_pool_pages=npp, chunk_tokens=dev_i32(n_c, device))
+    km.scatter_paged(dev(src, device), pool, dev_i32(pt, device), **kw)
+    back = dev(np.full(src.shape, SENTINEL, np.uint16), device)
+    km.gather_paged(back, pool, dev_i32(pt, device), **kw)
+    torch.cuda.synchronize()
+    want = np.full((L, npp * P, 8 * vecs), SENTINEL, np.uint16)
+    rows = np.full(src.shape, SENTINEL, np.uint16)
+    for c in range(C):
+        i = np.arange(n_c[c])
+        want[:, pt[c][i // P] * P + i % P] = src[c][:, i]
+        rows[c][:, i] = src[c][:, i]
+    assert np.array_equal(bits(pool), want)
+    assert np.array_equal(bits(back), rows)
 
 
 def test_gather_is_bit_exact_inverse(device):
