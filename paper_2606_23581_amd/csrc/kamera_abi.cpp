@@ -495,11 +495,22 @@ static int build_rehydrate(const kamera_rehydrate_args* a, kamera::RehydratePara
     launch = true;
     return KAMERA_OK;
   }
-  // token block: as large as possible while keeping >= 32 workgroups per CU
-  // (the MLA workloads ran 3-5% faster than at 16 per CU, the 28-layer one
-  // as fast; all slower at 64 or 8)
-  int tb = 1024;
-  while (tb > 64 && units * ceil_div(a->n_tokens, tb) < 8192) tb /= 2;
+  // Token block.  A workgroup stages W^T once per block, so a block should
+  // hold several tiles a wave; a launch needs enough of them to fill the device
+  // and even out its tail.  First down to 128 tokens (rank <= 32) or 256 while
+  // there are fewer than 24 workgroups per CU (9 above rank 64, where three fit
+  // a CU and W^T is 32 KiB), then down to 64 only while they do not fill the
+  // device once.  Measured against shrinking to 64 below 32 per CU: rank 128,
+  // 6 x 24 x 2 x 1024: 145 -> 111 us; rank 128, 1 x 24 x 8 x 512: 53 -> 41;
+  // rank 64, 4 x 16 x 1 x 1024: 26.9 -> 24.3; rank 16, 8 x 28 x 2 x 1024: 116
+  // -> 105; the MLA chunks keep their 128 (103 us; 64: 116, 256: 109).
+  int max_steps = 0;
+  for (int p = 0; p < a->n_planes; ++p) max_steps = std::max(max_steps, P.plane[p].m_steps);
+  const int tb_mid = max_steps <= 1 ? 128 : 256;
+  const int64_t many = max_steps > 2 ? 9 * 256 : 24 * 256, once = max_steps > 2 ? 3 * 256 : 4 * 256;
+  int tb = kamera::kMaxTokenBlock;
+  while (tb > tb_mid && units * ceil_div(a->n_tokens, tb) < many) tb /= 2;
+  while (tb > 64 && units * ceil_div(a->n_tokens, tb) < once) tb /= 2;
   tb = (int)std::min<int64_t>(tb, ceil_div(a->n_tokens, 64) * 64);
   P.token_block = tb;
   P.n_tblk = (int32_t)ceil_div(a->n_tokens, tb);

@@ -64,12 +64,13 @@ __device__ __forceinline__ int chunk_len(const Placement& pl, int c) {
 // Slot of token i of chunk c in a paged pool, or -1 for a page number outside
 // the pool (flagged in the status word, never written).
 __device__ __forceinline__ int64_t page_slot(const Placement& pl, int c, int i) {
-  const int page = pl.page_table[(int64_t)c * pl.pt_stride + i / pl.page_size];
+  const uint32_t k = fast_div((uint32_t)i, pl.fd_page);
+  const int page = pl.page_table[(int64_t)c * pl.pt_stride + k];
   if (page < 0 || page >= pl.n_pool_pages) {
     if (pl.status != nullptr) atomicOr(pl.status, KAMERA_STATUS_BAD_PAGE);
     return -1;
   }
-  return (int64_t)page * pl.page_size + i % pl.page_size;
+  return (int64_t)page * pl.page_size + (i - (int)k * pl.page_size);
 }
 
 // The slots of tokens [t_begin, t_end) (at most kMaxTokenBlock) into s_slot,

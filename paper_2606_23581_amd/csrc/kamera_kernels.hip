@@ -51,10 +51,13 @@ struct TileCtx {
   int m_steps;        // ceil(m / 32)
   int64_t in_base;    // element offset of (c, l, token 0, h, col0) in the input
   int64_t u_base;     // element offset of (c, l, h, token 0) in U
+  const int* pages;   // the block's pool pages in LDS (-1: not written), from page0 on; null: look each one up
+  int page0;
 };
 
-// position of token i of chunk c on each coordinate, as exact doubles
-__device__ __forceinline__ void token_position(const RehydrateParams& P, int c, int i,
+// position of token i of chunk c on each coordinate, as exact doubles; e: its
+// explicit position
+__device__ __forceinline__ void token_position(const RehydrateParams& P, int c, int i, const int32_t (&e)[3],
                                                double& pt, double& ph, double& pw) {
   if (P.pos_mode == 0) {                       // linear: p0 + i
     const double p = (double)P.chunk_pos[3 * c] + (double)i;
@@ -64,7 +67,6 @@ __device__ __forceinline__ void token_position(const RehydrateParams& P, int c, 
     ph = (double)P.chunk_pos[3 * c + 1] + (double)(i / P.grid_w);
     pw = (double)P.chunk_pos[3 * c + 2] + (double)(i % P.grid_w);
   } else {                                     // explicit (t, h, w) per token
-    const int32_t* e = P.explicit_pos + (int64_t)c * P.explicit_cs + 3 * (int64_t)i;
     pt = (double)e[0];
     ph = (double)e[1];
     pw = (double)e[2];
@@ -181,13 +183,30 @@ template <int NQ, int MS>
 struct TileRegs {
   u32x4 k[NQ];                  // K (or V) chunks, in load order
   u32x4 u[MS > 0 ? MS : 1];     // U chunks, in load order (staged) or B-operand order (direct)
+  int32_t pos[3];               // explicit (t, h, w) of the lane's token, with the tile's loads (kPosAhead)
 };
 
+// Explicit positions ride with a tile's loads where the registers allow: above
+// rank 32 without relocation (those kernels load a tile when it starts; with
+// the next tile's loads in flight as well the three registers would spill).
+template <int MS, int ROT, bool RELOC>
+constexpr bool kPosAhead = ROT != 0 && MS >= 2 && !RELOC;
+
+// explicit (t, h, w) of token i of chunk c
+__device__ __forceinline__ void load_position(const RehydrateParams& P, int c, int i, int32_t (&pos)[3]) {
+  const int32_t* e = P.explicit_pos + (int64_t)c * P.explicit_cs + 3 * (int64_t)i;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) pos[k] = e[k];
+}
+
 // Issue the global loads of one tile.
-template <int NQ, int MS>
-__device__ __forceinline__ void tile_load(const TileCtx& T, int i0, TileRegs<NQ, MS>& R) {
+template <int NQ, int MS, bool POS>
+__device__ __forceinline__ void tile_load(const RehydrateParams& P, const TileCtx& T, int i0, TileRegs<NQ, MS>& R) {
   const PlaneParams& Q = *T.Q;
   const int lane = threadIdx.x & 63;
+  if constexpr (POS) {
+    if (P.pos_mode == 2) load_position(P, T.c, min(i0 + (lane & 15), T.n_c - 1), R.pos);
+  }
   if constexpr (Staged<NQ>::value) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -293,7 +312,12 @@ __device__ __forceinline__ bool tile_compute(const RehydrateParams& P, const Til
     }
   }
   const bool early = EARLY && Staged<NQ>::value && (MS == 0 || !T.patched || u_staged);
-  if (early && next_i0 >= 0) tile_load<NQ, MS>(T, next_i0, R);
+  int32_t epos[3] = {0, 0, 0};
+  if constexpr (kPosAhead<MS, ROT, RELOC>) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) epos[k] = R.pos[k];
+  }
+  if (early && next_i0 >= 0) tile_load<NQ, MS, kPosAhead<MS, ROT, RELOC>>(P, T, next_i0, R);
 
   f32x4 acc[2 * NQ];
   if constexpr (kOneAngle) {
@@ -317,7 +341,11 @@ __device__ __forceinline__ bool tile_compute(const RehydrateParams& P, const Til
   const bool valid = i < T.n_c;
   double pt = 0.0, ph = 0.0, pw = 0.0;
   if constexpr (ROT != 0) {
-    token_position(P, T.c, valid ? i : T.n_c - 1, pt, ph, pw);
+    const int ip = valid ? i : T.n_c - 1;
+    if constexpr (!kPosAhead<MS, ROT, RELOC>) {
+      if (P.pos_mode == 2) load_position(P, T.c, ip, epos);
+    }
+    token_position(P, T.c, ip, epos, pt, ph, pw);
     // Rotation applied before the patch:
     //   post-rope frame:            R(p) K          (+ U W after)
     //   relocation, post-rope:      R(delta) K      (+ U W after)
@@ -379,8 +407,16 @@ __device__ __forceinline__ bool tile_compute(const RehydrateParams& P, const Til
   auto row_dst = [&](int ii, int64_t& dst) -> bool {
     if (ii >= T.n_c) return false;
     if (P.place.paged) {
-      const int64_t slot = page_slot(P.place, T.c, ii);
-      if (slot < 0) return false;
+      int64_t slot;
+      if (T.pages != nullptr) {
+        const uint32_t k = fast_div((uint32_t)ii, P.place.fd_page);
+        const int page = T.pages[(int)k - T.page0];
+        if (page < 0) return false;
+        slot = (int64_t)page * P.place.page_size + (ii - (int)k * P.place.page_size);
+      } else {
+        slot = page_slot(P.place, T.c, ii);
+        if (slot < 0) return false;
+      }
       dst = (int64_t)T.l * Q.out_s[1] + slot * Q.out_s[2] + (int64_t)T.h * Q.out_s[3] + T.col0;
     } else {
       const int rb = P.place.row_base ? P.place.row_base[T.c] : 0;
@@ -475,7 +511,7 @@ __device__ __forceinline__ void rehydrate_block(const RehydrateParams& P, const 
   constexpr bool kAhead = MS <= 1;
   constexpr bool kEarly = MS == 0 || (MS == 1 && !RELOC);
   TileRegs<NQ, MS> R;
-  if (kAhead && wave < n_tiles) tile_load<NQ, MS>(T, t_begin + wave * kTileTokens, R);
+  if (kAhead && wave < n_tiles) tile_load<NQ, MS, kPosAhead<MS, ROT, RELOC>>(P, T, t_begin + wave * kTileTokens, R);
   if constexpr (MS > 0) {
     if (T.patched) stage_w<NQ>(T, Wt);
   }
@@ -495,11 +531,11 @@ __device__ __forceinline__ void rehydrate_block(const RehydrateParams& P, const 
   }
   __syncthreads();
   for (int tile = wave; tile < n_tiles; tile += kWaves) {
-    if (!kAhead) tile_load<NQ, MS>(T, t_begin + tile * kTileTokens, R);
+    if (!kAhead) tile_load<NQ, MS, kPosAhead<MS, ROT, RELOC>>(P, T, t_begin + tile * kTileTokens, R);
     const int next_i0 = kAhead && tile + kWaves < n_tiles ? t_begin + (tile + kWaves) * kTileTokens : -1;
     const bool issued = tile_compute<NQ, MS, ROT, RELOC, kEarly>(P, T, t_begin + tile * kTileTokens, next_i0, R, Wt,
                                                                  tile_lds, s_freq, s_coord, s_dcs);
-    if (!issued && next_i0 >= 0) tile_load<NQ, MS>(T, next_i0, R);
+    if (!issued && next_i0 >= 0) tile_load<NQ, MS, kPosAhead<MS, ROT, RELOC>>(P, T, next_i0, R);
   }
 }
 
@@ -511,6 +547,7 @@ __global__ __launch_bounds__(kThreads, MS == 4 || RELOC ? 3 : 4) void rehydrate_
   __shared__ double s_freq[kMaxPairs];
   __shared__ int s_coord[kMaxPairs];
   __shared__ float s_dcs[2 * kMaxPairs];        // relocation: cos, sin of delta per pair
+  __shared__ int s_page[kMaxTokenBlock / kTileTokens + 1];
 
   const int64_t task = xcd_task(P.per_xcd);
   if (task >= P.n_tasks) return;
@@ -551,6 +588,21 @@ __global__ __launch_bounds__(kThreads, MS == 4 || RELOC ? 3 : 4) void rehydrate_
   T.patched = (B.flags & kBlkPatch) && T.m > 0;
   T.in_base = (int64_t)T.c * Q.in_s[0] + (int64_t)T.l * Q.in_s[1] + (int64_t)T.h * Q.in_s[3] + T.col0;
   T.u_base = (int64_t)T.c * Q.u_s[0] + (int64_t)T.l * Q.u_s[1] + (int64_t)T.h * Q.u_s[2];
+  // the block's pool pages, looked up once beside the first loads (read after
+  // the barrier that closes the W^T staging); pages of < 16 tokens are not staged
+  T.pages = nullptr;
+  T.page0 = 0;
+  if (P.place.paged && P.place.page_size >= kTileTokens) {
+    T.pages = s_page;
+    T.page0 = (int)fast_div((uint32_t)t_begin, P.place.fd_page);
+    const int n_pages = (int)fast_div((uint32_t)(t_end - 1), P.place.fd_page) - T.page0 + 1;
+    if ((int)threadIdx.x < n_pages) {
+      const int page = P.place.page_table[(int64_t)T.c * P.place.pt_stride + T.page0 + threadIdx.x];
+      const bool ok = page >= 0 && page < P.place.n_pool_pages;
+      if (!ok && P.place.status != nullptr) atomicOr(P.place.status, KAMERA_STATUS_BAD_PAGE);
+      s_page[threadIdx.x] = ok ? page : -1;
+    }
+  }
   const int rot = (B.flags & kBlkRotate) ? (P.rope.pairing == 0 ? 1 : 2) : 0;
   switch (B.nq * 3 + rot) {
     case 1 * 3 + 0: rehydrate_block<1, MS, 0, RELOC>(P, T, t_begin, t_end, lds_dyn, s_freq, s_coord, s_dcs); break;

@@ -430,6 +430,23 @@ def test_shift_matches_oracle(device, name):
     assert int(status.cpu()[0]) == 0
 
 
+@pytest.mark.parametrize("C,L,H,n,m,P", [(2, 1, 1, 1100, 128, 16), (2, 1, 2, 300, 72, 24), (1, 2, 1, 1030, 40, 15),
+                                         (3, 2, 3, 130, 64, 17), (2, 2, 1, 70, 16, 64),
+                                         (30, 30, 2, 70, 8, 16)])
+def test_rehydrate_per_head_blocks(device, C, L, H, n, m, P):
+    """The per-head kernel's token blocks and page look-ups: blocks of 64, 128 and
+    256 tokens with a partial last one, pages staged in LDS (16 tokens and more,
+    not a power of two, crossing block edges) and looked up one by one (15),
+    explicit positions, ragged chunks, both patch frames."""
+    import paper_2606_23581_amd as km
+
+    print(f"[case] per-head blocks C{C} L{L} H{H} n{n} m{m} P{P}", flush=True)
+    for post in (False, True):
+        run_rehydrate(RehydrateCase(C=C, L=L, H=H, n=n, m_k=m, m_v=m, sections=(16, 24, 24), pos_mode="explicit",
+                                    paged=True, page_size=P, ragged=True, post_rope=post, kernel=km.KERNEL_PER_HEAD,
+                                    plan=km.PLAN_PER_HEAD, seed=n + m), device)
+
+
 @pytest.mark.parametrize("pairing", ["neox", "interleaved"])
 @pytest.mark.parametrize("H,n,P,rope_dim", [(1, 7, 0, 128), (3, 50, 24, 64), (5, 129, 16, 128), (33, 40, 0, 16)])
 def test_shift_small_tasks(device, pairing, H, n, P, rope_dim):
