@@ -362,25 +362,21 @@ __device__ __forceinline__ float tw_down(const float* __restrict__ b, float* __r
 __device__ __forceinline__ int tri_slot(int c, int p) { return c * kTriRows + 8 * (p ^ (((c >> 3) ^ (c >> 4)) & 1)); }
 
 // Rows i0 .. i0 + 7 (the same on every lane of a wave) of column j of the
-// (orbit-mean) deficit: zero past n rows or d columns.  A row past n is read
-// at row n - 1 and dropped, so there is no branch per row.  Orbit members are
-// read two at a time, all their loads issued before the sums, which keep the
-// members' order.
+// (orbit-mean) deficit.  A row past n is read at row n - 1, so that every call
+// issues the same loads (a load behind a branch would make the compiler wait
+// for all the loads in flight).  Orbit members are read two at a time, all
+// their loads issued before the sums, which keep the members' order.
+template <bool ORBIT>
 __device__ __forceinline__ void tri_load8(const FormParams& P, const float* delta, int i0, uint32_t j, int n,
                                           float (&x)[8]) {
   const int64_t s3 = P.delta_s[3];
   const float* row[8];
-  if (i0 + 8 <= n) {
-    row[0] = delta + (int64_t)i0 * s3;
+  row[0] = delta + (int64_t)min(i0, n - 1) * s3;
 #pragma unroll
-    for (int e = 1; e < 8; ++e) row[e] = row[e - 1] + s3;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) row[e] = delta + (int64_t)min(i0 + e, n - 1) * s3;
-  }
+  for (int e = 1; e < 8; ++e) row[e] = row[e - 1] + (i0 + e < n ? s3 : 0);
 #pragma unroll
   for (int e = 0; e < 8; ++e) x[e] = row[e][j];
-  if (P.n_orbit > 1) {
+  if constexpr (ORBIT) {
     for (int o = 1; o < P.n_orbit; o += 2) {
       const bool two = o + 1 < P.n_orbit;
       const int64_t o1 = (int64_t)o * P.orbit_s, o2 = two ? o1 + P.orbit_s : o1;
@@ -396,81 +392,82 @@ __device__ __forceinline__ void tri_load8(const FormParams& P, const float* delt
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] *= P.inv_orbit;
   }
-  if (i0 + 8 > n) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (i0 + e >= n) x[e] = 0.f;
-  }
 }
 
 // ---- 1. G = Delta^T Delta: tiles (I, J), I < NB, into acc ----
 // Stages of kTriRows = 16 rows (one MFMA k-step) in two LDS buffers, one
 // barrier each: thread (sg, c) splits rows 8 sg .. 8 sg + 7 of column c of
-// stage s + 1 into three bf16 parts while the products of stage s run.  Its
+// stage s + 1 into three bf16 parts between the products of stage s.  Its
 // loads are issued kTriAhead stages before: a unit alone on its CU is bound by
 // the memory latency (1024 x 128: 61 us with 32-row stages loaded one ahead, 54 us
 // with these).
 constexpr int kTriAhead = 3;
 
-template <int NB>
+template <int NB, bool ORBIT>
 __device__ __forceinline__ void tri_gram(const FormParams& P, const float* delta, int J, uint16_t* Tb,
                                          f32x16v (&acc)[NB]) {
   constexpr int kPart = 32 * NB * kTriRows;
   const int tid = threadIdx.x, lane = tid & 63;
   const int n = P.n_tokens, d = P.dim;
   const int sc = tid & 127, sg = __builtin_amdgcn_readfirstlane(tid >> 7);
-  const bool cin = sc < d, stager = NB == 4 || sc < 32 * NB;
+  const bool cin = sc < d;
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[I][r] = 0.f;
   const int ns = (n + kTriRows - 1) / kTriRows;
+  const uint32_t cc = (uint32_t)min(sc, d - 1);
   float x[kTriAhead][8];
 #pragma unroll
-  for (int a = 0; a < kTriAhead; ++a) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[a][e] = 0.f;
-    if (a < ns && cin) tri_load8(P, delta, kTriRows * a + 8 * sg, sc, n, x[a]);
-  }
+  for (int a = 0; a < kTriAhead; ++a) tri_load8<ORBIT>(P, delta, kTriRows * a + 8 * sg, cc, n, x[a]);
   uint16_t* const mine = Tb + tri_slot(sc, sg);
-  auto put = [&](const float (&y)[8], int buf) {
-    if (stager) {
-      u32x4v hi, mid, lo;
-      split3_bf16x8(y, hi, mid, lo);
-      uint16_t* q = mine + buf * 3 * kPart;
+  auto put = [&](float (&y)[8], int s, int buf) {
+    if (kTriRows * (s + 1) > n || 32 * NB > d) {   // zeros past n rows or d columns
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = kTriRows * s + 8 * sg + e < n && cin ? y[e] : 0.f;
+    }
+    u32x4v hi, mid, lo;
+    split3_bf16x8(y, hi, mid, lo);
+    uint16_t* q = mine + buf * 3 * kPart;
+    if (NB == 4 || sc < 32 * NB) {
       *reinterpret_cast<u32x4v*>(q) = hi;
       *reinterpret_cast<u32x4v*>(q + kPart) = mid;
       *reinterpret_cast<u32x4v*>(q + 2 * kPart) = lo;
     }
   };
-  // stage s: its registers (set s % kTriAhead) go to LDS, the loads of stage
-  // s + kTriAhead are issued into them, then the products
+  put(x[0], 0, 0);
+  tri_load8<ORBIT>(P, delta, kTriRows * kTriAhead + 8 * sg, cc, n, x[0]);
+  // stage s: y holds stage s + 1, split into the other buffer between the
+  // products (past the last stage: zeros, never read), then takes the loads of stage s + 1 + kTriAhead.  The buffer it writes was
+  // read in stage s - 1, before the barrier.
   auto stage = [&](int s, float (&y)[8]) {
     const int buf = s & 1;
-    put(y, buf);
     __syncthreads();
-    if (s + kTriAhead < ns && cin) tri_load8(P, delta, kTriRows * (s + kTriAhead) + 8 * sg, sc, n, y);
-    if (J >= NB) return;
     const uint16_t* const Ts = Tb + buf * 3 * kPart;
     const int p = lane >> 5, c = lane & 31;
-    bf16x8v b[3];
+    if (NB == 4 || J < NB) {
+      bf16x8v b[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) b[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * J + c, p));
+      for (int q = 0; q < 3; ++q) b[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * J + c, p));
 #pragma unroll
-    for (int I = 0; I < NB; ++I) {
-      constexpr int kA[6] = {1, 0, 2, 0, 1, 0}, kB[6] = {1, 2, 0, 1, 0, 0};   // smallest products first
-      bf16x8v a[3];
+      for (int I = 0; I < NB; ++I) {
+        constexpr int kA[6] = {1, 0, 2, 0, 1, 0}, kB[6] = {1, 2, 0, 1, 0, 0};   // smallest products first
+        bf16x8v a[3];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * I + c, p));
+        for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * I + c, p));
 #pragma unroll
-      for (int r = 0; r < 6; ++r) acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kA[r]], b[kB[r]], acc[I], 0, 0, 0);
+        for (int r = 0; r < 6; ++r)
+          acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kA[r]], b[kB[r]], acc[I], 0, 0, 0);
+        if (I == 0 && NB == 4) put(y, s + 1, buf ^ 1);
+      }
     }
+    if (NB < 4) put(y, s + 1, buf ^ 1);
+    tri_load8<ORBIT>(P, delta, kTriRows * (s + 1 + kTriAhead) + 8 * sg, cc, n, y);
   };
-  // (a stage's buffer is written two stages after it was read, with a barrier between)
+  // (whole groups of kTriAhead stages, the last ones of zeros: no branch between them)
   for (int s = 0; s < ns; s += kTriAhead) {
 #pragma unroll
-    for (int a = 0; a < kTriAhead; ++a)
-      if (s + a < ns) stage(s + a, x[a]);
+    for (int a = 0; a < kTriAhead; ++a) stage(s + a, x[(a + 1) % kTriAhead]);
   }
 }
 
@@ -510,6 +507,21 @@ __device__ __forceinline__ void half_swap(float& a, float& b) {
 // No column is touched once it is reduced (v and w are zero there), so column
 // j keeps x_j below the diagonal: the reflector v_j but for its first entry,
 // which goes to v0.  The back-transformation takes the reflectors from there.
+// alpha, v's first entry and beta of the reflector of (x0, x) with |x|^2 = sq.
+// (hardware square root and reciprocal, 1 ulp each: beta is formed from the v
+// that is kept, so H is orthogonal to rounding; sq = 0: already reduced, H = I)
+__device__ __forceinline__ void tri_scales(float x0, float sq, float& alpha, float& v0, float& beta) {
+  const float nrm = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sq));
+  alpha = sq != 0.f ? (x0 >= 0.f ? -nrm : nrm) : x0;
+  v0 = x0 - alpha;
+  beta = sq != 0.f ? 2.f * __builtin_amdgcn_rcpf(fmaf(v0, v0, sq)) : 0.f;
+}
+
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+};
+
 struct TriVec {
   float v0, v1;          // v_j, entries lane and 64 + lane (v0 unused once j + 1 >= 64)
   float beta;
@@ -522,49 +534,35 @@ __device__ __forceinline__ float tri_at(float x0, float x1, int i) { return lane
 constexpr int kTriScr = 512 + 512;
 
 // The reflector of column jn <= d - 2 from its updated row (r0, r1), x0 =
-// row[jn + 1]; the wave's v_jn goes to its private vbuf.  The wave `writer`
-// also stores T's entries.  HI: entries below 64 are all reduced.
-template <int NB, bool HI>
-__device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r1, float x0, float* vbuf, bool writer,
-                                            float* s_a, float* s_b, float* s_beta, float* s_v0) {
+// row[jn + 1]; the wave's v_jn goes to its private vbuf.  mid1 and mid2 are run
+// inside the dependent chain (work for the matrix pipe, which issues in order
+// with it).
+template <int NB, typename F1, typename F2>
+__device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r1, float x0, float* vbuf, F1 mid1,
+                                            F2 mid2) {
   const int lane = threadIdx.x & 63;
-  const float q0 = !HI && lane > jn + 1 ? r0 : 0.f;
+  const float q0 = lane > jn + 1 ? r0 : 0.f;
   const float q1 = lane + 64 > jn + 1 ? r1 : 0.f;
-  const float sq = tri_wave_sum(HI ? q1 * q1 : (NB > 2 ? fmaf(q0, q0, q1 * q1) : q0 * q0));
-  // (hardware square root and reciprocal, 1 ulp each: beta is formed from the
-  // v that is kept, so H stays orthogonal to rounding; sq = 0: already
-  // reduced, H_j = I)
-  const float nrm = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sq));
-  const float alpha = sq != 0.f ? (x0 >= 0.f ? -nrm : nrm) : x0;
-  const float v0 = x0 - alpha;
-  const float beta = sq != 0.f ? 2.f * __builtin_amdgcn_rcpf(fmaf(v0, v0, sq)) : 0.f;
-  if (!HI) {
-    S.v0 = lane == jn + 1 ? v0 : q0;
-    vbuf[lane] = S.v0;
-  }
+  const float part = NB > 2 ? fmaf(q0, q0, q1 * q1) : q0 * q0;
+  mid1();
+  const float sq = tri_wave_sum(part);
+  float v0, alpha;
+  tri_scales(x0, sq, alpha, v0, S.beta);
+  mid2();
+  S.v0 = lane == jn + 1 ? v0 : q0;
+  vbuf[lane] = S.v0;
   if (NB > 2) {
     S.v1 = lane + 64 == jn + 1 ? v0 : q1;
     vbuf[64 + lane] = S.v1;
-  }
-  S.beta = beta;
-  if (writer) {
-    if (lane == (jn & 63)) s_a[jn] = HI || jn >= 64 ? r1 : r0;
-    if (lane == 0) {
-      s_b[jn] = alpha;
-      s_beta[jn] = beta;
-      s_v0[jn] = v0;
-    }
   }
 }
 
 // Steps 0 .. d - 3.  A wave runs those of its own and earlier blocks, then
 // clears its p in both buffers and only keeps the barriers.
 template <int NB>
-__device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, int d, float* scr, float* s_a,
-                                          float* s_b, float* s_beta, float* s_v0) {
+__device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, int d, float* scr) {
   const int lane = threadIdx.x & 63;
   const int col = 32 * J + (lane & 31);
-  const bool writer = J == NB - 1;
   float* const vbuf = scr + 512 + 128 * J;
   const float* const vrow = vbuf + 4 * (lane >> 5);
   const int j_own = J < NB ? min(32 * J + 31, d - 2) : 0;
@@ -614,21 +612,27 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
     const float K = 0.5f * S.beta * S.beta * pv;
     const float w0 = fmaf(-K, S.v0, S.beta * p0), w1 = fmaf(-K, S.v1, S.beta * p1);
     // the update's operands: lanes < 32 v (w for B), others w (v), of a block
-    {
-      float b0 = J >= 2 ? w1 : w0, b1 = J >= 2 ? S.v1 : S.v0;
-      half_swap(b0, b1);
-      const float bop = -((J & 1) ? b1 : b0);
-      float a[4] = {S.v0, w0, S.v1, w1};
-      half_swap(a[0], a[1]);
-      if (NB > 2) half_swap(a[2], a[3]);
-#pragma unroll
-      for (int I = 0; I < NB; ++I)
+    float b0 = J >= 2 ? w1 : w0, b1 = J >= 2 ? S.v1 : S.v0;
+    half_swap(b0, b1);
+    const float bop = -((J & 1) ? b1 : b0);
+    float a[4] = {S.v0, w0, S.v1, w1};
+    half_swap(a[0], a[1]);
+    if (NB > 2) half_swap(a[2], a[3]);
+    // tile I's update; they are issued one at a time inside the chains below,
+    // as an MFMA holds up what follows it until the one before is through
+    auto update = [&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      if constexpr (I >= 0 && I < NB) {
         if (I >= ib) acc[I] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[I], bop, acc[I], 0, 0, 0);
-    }
+      }
+    };
+    update(IntC<NB - 1>{});
     const float vj = tri_at(S.v0, S.v1, j + 1), wj = tri_at(w0, w1, j + 1);
     r0 = fmaf(-vj, w0, fmaf(-wj, S.v0, r0));
     if (NB > 2) r1 = fmaf(-vj, w1, fmaf(-wj, S.v1, r1));
-    tri_reflect<NB, false>(S, j + 1, r0, r1, tri_at(r0, r1, j + 2), vbuf, writer, s_a, s_b, s_beta, s_v0);
+    tri_reflect<NB>(S, j + 1, r0, r1, tri_at(r0, r1, j + 2), vbuf, [&] { update(IntC<NB - 2>{}); },
+                    [&] { update(IntC<NB - 3>{}); });
+    update(IntC<NB - 4>{});
   }
   for (int j = j_own; j < d - 2; ++j) {
     if (J < NB && j < j_own + 2 && lane < 32) scr[256 * (j & 1) + col] = 0.f;
@@ -636,6 +640,11 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
   }
 }
 
+// Leaves T's diagonal and subdiagonal in s_a and s_b, the reflectors' scales
+// in s_beta (zero past the last) and first entries in s_v0.  They are taken from
+// the columns as they are kept, after the steps (a step's own values are those
+// of the row, equal but for rounding): nothing but the chain is left in a step,
+// and V and beta agree to rounding however small x is.
 template <int NB>
 __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, float* scr, float* s_a, float* s_b,
                                            float* s_beta, float* s_v0) {
@@ -649,13 +658,37 @@ __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, flo
   if (J < NB && lane < 32) rb[32 * J + lane] = acc[0][0];
   __syncthreads();
   if (J < NB)
-    tri_reflect<NB, false>(S, 0, rb[lane], rb[64 + lane], lane_f(rb[lane], 1), scr + 512 + 128 * J, J == NB - 1, s_a,
-                           s_b, s_beta, s_v0);
-  tri_steps<NB>(acc, S, J, d, scr, s_a, s_b, s_beta, s_v0);
-  // the last diagonal entry: all updates are in the tile (reflector d - 2 is the identity)
-  const int rr = (d - 1) & 31;
-  const float last = acc[NB - 1][((rr >> 3) << 2) | (rr & 3)];
-  if (J == NB - 1 && lane == rr + 32 * ((rr >> 2) & 1)) s_a[d - 1] = last;
+    tri_reflect<NB>(S, 0, rb[lane], rb[64 + lane], lane_f(rb[lane], 1), scr + 512 + 128 * J, [] {}, [] {});
+  tri_steps<NB>(acc, S, J, d, scr);
+  if (J < NB) {
+    // column j of this lane: a_j = A[j][j], x_0 = A[j + 1][j], |x|^2 below it
+    const int c = lane & 31, h4 = 4 * (lane >> 5), j = 32 * J + c;
+    float aj = 0.f, x0 = 0.f, sq = 0.f;
+#pragma unroll
+    for (int I = 0; I < NB; ++I) {
+      if (I < J) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = 32 * I + 8 * (r >> 2) + (r & 3) + h4;
+        const float x = acc[I][r];
+        if (I == J) aj += i == j ? x : 0.f;
+        if (I == J || (I == J + 1 && r == 0)) x0 += i == j + 1 ? x : 0.f;
+        sq += i > j + 1 ? x * x : 0.f;
+      }
+    }
+    float aj2 = aj, x02 = x0, sq2 = sq;
+    half_swap(aj, aj2);
+    half_swap(x0, x02);
+    half_swap(sq, sq2);
+    float alpha, v0, beta;
+    tri_scales(x0 + x02, sq + sq2, alpha, v0, beta);
+    if (lane < 32 && j < d) {
+      s_a[j] = aj + aj2;
+      s_b[j] = alpha;                          // (column d - 2: sq = 0, alpha = A[d - 1][d - 2])
+      if (j < d - 2) s_beta[j] = beta;
+      s_v0[j] = v0;
+    }
+  }
 }
 
 // ---- 2b. compact WY form of the reflectors ----
@@ -768,9 +801,10 @@ __device__ __forceinline__ int sturm_count(const float* s_as, const float* s_bs,
       }
       const float mx = fmaxf(fabsf(p1), fabsf(p0));
       low = fminf(low, mx);
-      const int e = -__builtin_amdgcn_frexp_expf(mx);
-      p1 = __builtin_amdgcn_ldexpf(p1, e);
-      p0 = __builtin_amdgcn_ldexpf(p0, e);
+      // times the power of two that brings mx to [2, 4)
+      const float sc = __uint_as_float(0x7f800000u - (__float_as_uint(mx) & 0x7f800000u));
+      p1 *= sc;
+      p0 *= sc;
     }
     cnt += __popc((bits ^ (bits >> 1)) & 0xffffu);
   }
@@ -894,8 +928,13 @@ __global__ __launch_bounds__(kTriThreads, 4) void form_tri_kernel(const FormPara
   int* const s_fail = reinterpret_cast<int*>(s_misc + 2);
 
   f32x16v acc[NB];
-  tri_gram<NB>(P, P.delta + (int64_t)c * P.delta_s[0] + (int64_t)l * P.delta_s[1] + (int64_t)h * P.delta_s[2], J,
-               reinterpret_cast<uint16_t*>(Z), acc);
+  {
+    const float* const delta =
+        P.delta + (int64_t)c * P.delta_s[0] + (int64_t)l * P.delta_s[1] + (int64_t)h * P.delta_s[2];
+    uint16_t* const Tb = reinterpret_cast<uint16_t*>(Z);
+    if (P.n_orbit > 1) tri_gram<NB, true>(P, delta, J, Tb, acc);
+    else tri_gram<NB, false>(P, delta, J, Tb, acc);
+  }
   tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta, s_v0);
   __syncthreads();
   tri_wy<NB>(acc, J, d, Z + kTriScr + 32 * kSLd * J, s_beta, s_v0);
