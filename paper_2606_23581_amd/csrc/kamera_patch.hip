@@ -650,7 +650,7 @@ size_t form_lds_bytes(int dim, int /*m*/) {
 
 // ---------------------------------------------------------------------------
 // U = Delta W^T, the factor's token side, from the W form_patch_kernel has
-// stored (so U W is formed from exactly the kept W).  A wave takes kURows
+// stored (so U W is formed from exactly the kept W).  A wave takes ROWS
 // token rows of one unit, as 16-row tiles, and the ranks 64 at a time (the
 // workgroup's four waves share those 64 W rows, staged once in LDS); the
 // products are 16x16x32 bf16 MFMAs with fp32 accumulation.  Delta is read in
@@ -660,18 +660,22 @@ size_t form_lds_bytes(int dim, int /*m*/) {
 // the same slots (B operand), and rows 4 kg .. 4 kg + 3 of rank t of the
 // product.  With an orbit the members' rows are averaged in fp32 first.
 // ---------------------------------------------------------------------------
-constexpr int kURows = 64;            // token rows per wave
+// token rows per wave: 64, so that the W rows a workgroup stages serve 256
+// token rows; 16 while the launch then has fewer than 512 workgroups (two per
+// CU) -- 8 units of 1024 rows: 15.5 us with 64, 6.4 with 16
+constexpr int kURowsMany = 64, kURowsFew = 16;
 constexpr int kUThreads = 256;
-constexpr int kURowsPerBlock = kURows * (kUThreads / 64);
 constexpr int kUWLd = 144;            // bf16 per staged W row: 288 bytes, so the B-operand reads
                                       // of a half wave (16 rows x 2 pieces) fall on distinct banks
 
+template <int ROWS>
 __global__ __launch_bounds__(kUThreads) void form_u_kernel(const FormParams /*by value, read in place*/) {
   const FormParams& P = *static_cast<const FormParams*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t = lane & 15, kg = lane >> 4;
   const int n = P.n_tokens, d = P.dim, m = P.m;
-  const uint32_t bpu = (uint32_t)((n + kURowsPerBlock - 1) / kURowsPerBlock);   // blocks per unit
+  constexpr int kRowsPerBlock = ROWS * (kUThreads / 64);
+  const uint32_t bpu = (uint32_t)((n + kRowsPerBlock - 1) / kRowsPerBlock);   // blocks per unit
   // workgroups go to the 8 XCDs in turn: block b takes the place
   // (b mod 8) * (grid / 8) + b / 8, so that the blocks of one unit share an
   // XCD and read its W from that XCD's L2 (the grid is a multiple of 8)
@@ -681,7 +685,7 @@ __global__ __launch_bounds__(kUThreads) void form_u_kernel(const FormParams /*by
   const int h = (int)(unit % (uint32_t)P.n_heads);
   const int l = (int)((unit / (uint32_t)P.n_heads) % (uint32_t)P.n_layers);
   const int c = (int)(unit / ((uint32_t)P.n_heads * (uint32_t)P.n_layers));
-  const int row0 = (int)(place - unit * bpu) * kURowsPerBlock + wave * kURows;
+  const int row0 = (int)(place - unit * bpu) * kRowsPerBlock + wave * ROWS;
   // (a wave past the unit's rows still takes part in the W staging)
   __shared__ __align__(16) uint16_t s_w[64 * kUWLd];
   const float* delta = P.delta + (int64_t)c * P.delta_s[0] + (int64_t)l * P.delta_s[1] + (int64_t)h * P.delta_s[2];
@@ -734,7 +738,7 @@ __global__ __launch_bounds__(kUThreads) void form_u_kernel(const FormParams /*by
     auto wb = [&](int ct, int s) {
       return *reinterpret_cast<const u32x4v*>(s_w + (16 * ct + t) * kUWLd + 32 * s + 8 * kg);
     };
-    for (int rt = 0; rt < kURows / 16; ++rt) {
+    for (int rt = 0; rt < ROWS / 16; ++rt) {
       const int i0 = row0 + 16 * rt;
       if (i0 >= n) break;                      // uniform in the wave (no barrier inside)
       float x[4][8];
@@ -803,6 +807,15 @@ static hipError_t launch_jacobi(const FormParams& p, uint32_t grid, hipStream_t 
   return hipGetLastError();
 }
 
+template <int ROWS>
+static hipError_t launch_u(const FormParams& p, hipStream_t s) {
+  constexpr int kRowsPerBlock = ROWS * (kUThreads / 64);
+  const int64_t bpu = (p.n_tokens + kRowsPerBlock - 1) / kRowsPerBlock;
+  const int64_t blocks = (bpu * p.n_units + 7) / 8 * 8;   // the places past the units return at once
+  hipLaunchKernelGGL((form_u_kernel<ROWS>), dim3((uint32_t)blocks), dim3(kUThreads), 0, s, p);
+  return hipGetLastError();
+}
+
 hipError_t launch_form_patch(const FormParams& p, hipStream_t s) {
   hipError_t e;
   if (p.sweeps > 0) {
@@ -814,10 +827,7 @@ hipError_t launch_form_patch(const FormParams& p, hipStream_t s) {
   }
   if (e != hipSuccess) return e;
   // U from the stored W, on the same stream: after the W of every unit
-  const int64_t bpu = (p.n_tokens + kURowsPerBlock - 1) / kURowsPerBlock;
-  const int64_t blocks = (bpu * p.n_units + 7) / 8 * 8;   // the places past the units return at once
-  hipLaunchKernelGGL(form_u_kernel, dim3((uint32_t)blocks), dim3(kUThreads), 0, s, p);
-  return hipGetLastError();
+  return (p.n_tokens + 255) / 256 * (int64_t)p.n_units < 512 ? launch_u<kURowsFew>(p, s) : launch_u<kURowsMany>(p, s);
 }
 
 }  // namespace kamera
