@@ -190,7 +190,8 @@ struct FormParams {
   int32_t w_vec;                    // W rows 16-byte aligned: 8 entries per load
   int32_t u_pair;                   // U rows 4-byte aligned: 2 ranks per store
   int32_t z_groups;                 // tridiagonal solver: LDS groups of 32 columns, set at launch
-  int32_t pad_;
+  int32_t unit_bytes;               // bytes of one unit's deficit from its first row on, where its rows do not
+                                    // overlap and it (with the stages read past its end) fits 31 bits; else 0
 };
 
 size_t form_lds_bytes(int dim, int m);

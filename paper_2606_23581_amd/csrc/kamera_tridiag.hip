@@ -361,22 +361,43 @@ __device__ __forceinline__ float tw_down(const float* __restrict__ b, float* __r
 // banks
 __device__ __forceinline__ int tri_slot(int c, int p) { return c * kTriRows + 8 * (p ^ (((c >> 3) ^ (c >> 4)) & 1)); }
 
-// Rows i0 .. i0 + 7 (the same on every lane of a wave) of column j of the
-// (orbit-mean) deficit.  A row past n is read at row n - 1, so that every call
-// issues the same loads (a load behind a branch would make the compiler wait
-// for all the loads in flight).  Orbit members are read two at a time, all
-// their loads issued before the sums, which keep the members' order.
-template <bool ORBIT>
-__device__ __forceinline__ void tri_load8(const FormParams& P, const float* delta, int i0, uint32_t j, int n,
-                                          float (&x)[8]) {
-  const int64_t s3 = P.delta_s[3];
-  const float* row[8];
-  row[0] = delta + (int64_t)min(i0, n - 1) * s3;
+// One deficit through a buffer descriptor: rows past n and lanes without a
+// column read zeros by its bounds check, and a row's address is one scalar
+// addition (64-bit row pointers took 123 scalar instructions a stage).  For
+// rows that do not overlap and a unit's rows within 2^31 bytes.
+struct TriRows {
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t col;            // byte offset of the lane's column (past the end: none)
+  int32_t row;             // bytes of a row
+  int32_t end;             // the descriptor's bytes: a row's offset stops there, where no lane is in range
+
+  __device__ __forceinline__ void load8(int i0, float (&x)[8]) const {
+    int32_t at = i0 * row;
 #pragma unroll
-  for (int e = 1; e < 8; ++e) row[e] = row[e - 1] + (i0 + e < n ? s3 : 0);
+    for (int e = 0; e < 8; ++e, at += row)
+      x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)col, min(at, end), 0));
+  }
+};
+
+// The general form, also the mean of an orbit's members: 64-bit row pointers.
+// A row past n is read at row n - 1, so that every call issues the same loads
+// (a load behind a branch would make the compiler wait for all the loads in
+// flight).  Orbit members are read two at a time, all their loads issued before
+// the sums, which keep the members' order.
+struct TriOrbit {
+  const FormParams& P;
+  const float* delta;
+  uint32_t j;
+
+  __device__ __forceinline__ void load8(int i0, float (&x)[8]) const {
+    const int64_t s3 = P.delta_s[3];
+    const int n = P.n_tokens;
+    const float* row[8];
+    row[0] = delta + (int64_t)min(i0, n - 1) * s3;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = row[e][j];
-  if constexpr (ORBIT) {
+    for (int e = 1; e < 8; ++e) row[e] = row[e - 1] + (i0 + e < n ? s3 : 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = row[e][j];
     for (int o = 1; o < P.n_orbit; o += 2) {
       const bool two = o + 1 < P.n_orbit;
       const int64_t o1 = (int64_t)o * P.orbit_s, o2 = two ? o1 + P.orbit_s : o1;
@@ -389,26 +410,28 @@ __device__ __forceinline__ void tri_load8(const FormParams& P, const float* delt
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = two ? (x[e] + y[e]) + z[e] : x[e] + y[e];
     }
+    if (P.n_orbit > 1) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] *= P.inv_orbit;
+      for (int e = 0; e < 8; ++e) x[e] *= P.inv_orbit;
+    }
   }
-}
+};
 
 // ---- 1. G = Delta^T Delta: tiles (I, J), I < NB, into acc ----
+// src: TriRows (ZEROS: it reads zeros past n rows or d columns) or TriOrbit.
 // Stages of kTriRows = 16 rows (one MFMA k-step) in two LDS buffers, one
 // barrier each: thread (sg, c) splits rows 8 sg .. 8 sg + 7 of column c of
-// stage s + 1 into three bf16 parts between the products of stage s.  Its
-// loads are issued kTriAhead stages before: a unit alone on its CU is bound by
-// the memory latency (1024 x 128: 61 us with 32-row stages loaded one ahead, 54 us
-// with these).
+// stage s + 1 into three bf16 parts while stage s is multiplied; its loads are
+// issued kTriAhead stages before.  A unit alone on its CU takes 46 us for 1024 x
+// 128 (61 us with 32-row stages loaded one ahead): one wave per SIMD issues the
+// split (13 us), the products (13) and the waits for LDS and memory in turn;
+// with four units on the CU they overlap.
 constexpr int kTriAhead = 3;
 
-template <int NB, bool ORBIT>
-__device__ __forceinline__ void tri_gram(const FormParams& P, const float* delta, int J, uint16_t* Tb,
-                                         f32x16v (&acc)[NB]) {
+template <int NB, bool ZEROS, typename SRC>
+__device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, uint16_t* Tb, f32x16v (&acc)[NB]) {
   constexpr int kPart = 32 * NB * kTriRows;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int n = P.n_tokens, d = P.dim;
   const int sc = tid & 127, sg = __builtin_amdgcn_readfirstlane(tid >> 7);
   const bool cin = sc < d;
 #pragma unroll
@@ -416,13 +439,12 @@ __device__ __forceinline__ void tri_gram(const FormParams& P, const float* delta
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[I][r] = 0.f;
   const int ns = (n + kTriRows - 1) / kTriRows;
-  const uint32_t cc = (uint32_t)min(sc, d - 1);
   float x[kTriAhead][8];
 #pragma unroll
-  for (int a = 0; a < kTriAhead; ++a) tri_load8<ORBIT>(P, delta, kTriRows * a + 8 * sg, cc, n, x[a]);
+  for (int a = 0; a < kTriAhead; ++a) src.load8(kTriRows * a + 8 * sg, x[a]);
   uint16_t* const mine = Tb + tri_slot(sc, sg);
   auto put = [&](float (&y)[8], int s, int buf) {
-    if (kTriRows * (s + 1) > n || 32 * NB > d) {   // zeros past n rows or d columns
+    if (!ZEROS && (kTriRows * (s + 1) > n || 32 * NB > d)) {   // zeros past n rows or d columns
 #pragma unroll
       for (int e = 0; e < 8; ++e) y[e] = kTriRows * s + 8 * sg + e < n && cin ? y[e] : 0.f;
     }
@@ -436,7 +458,7 @@ __device__ __forceinline__ void tri_gram(const FormParams& P, const float* delta
     }
   };
   put(x[0], 0, 0);
-  tri_load8<ORBIT>(P, delta, kTriRows * kTriAhead + 8 * sg, cc, n, x[0]);
+  src.load8(kTriRows * kTriAhead + 8 * sg, x[0]);
   // stage s: y holds stage s + 1, split into the other buffer between the
   // products (past the last stage: zeros, never read), then takes the loads of stage s + 1 + kTriAhead.  The buffer it writes was
   // read in stage s - 1, before the barrier.
@@ -449,20 +471,31 @@ __device__ __forceinline__ void tri_gram(const FormParams& P, const float* delta
       bf16x8v b[3];
 #pragma unroll
       for (int q = 0; q < 3; ++q) b[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * J + c, p));
+      // the tiles in pairs, whose chains of products alternate (a product waits
+      // about twice its own 32 cycles for the one before it in its chain): lo hi;
+      // mid mid, mid hi; hi lo, hi mid, hi hi, one part of A at a time
 #pragma unroll
-      for (int I = 0; I < NB; ++I) {
-        constexpr int kA[6] = {1, 0, 2, 0, 1, 0}, kB[6] = {1, 2, 0, 1, 0, 0};   // smallest products first
-        bf16x8v a[3];
+      for (int I0 = 0; I0 < NB; I0 += 4) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * I + c, p));
+        for (int q = 2; q >= 0; --q) {
+          bf16x8v av[4];
 #pragma unroll
-        for (int r = 0; r < 6; ++r)
-          acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kA[r]], b[kB[r]], acc[I], 0, 0, 0);
-        if (I == 0 && NB == 4) put(y, s + 1, buf ^ 1);
+          for (int u = 0; u < 4; ++u)
+            if (I0 + u < NB)
+              av[u] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * (I0 + u) + c, p));
+#pragma unroll
+          for (int t = 2 - q; t >= 0; --t)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (I0 + u < NB)
+                acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[t], acc[I0 + u], 0, 0, 0);
+        }
+        if (I0 == 0 && NB == 4) put(y, s + 1, buf ^ 1);
       }
     }
     if (NB < 4) put(y, s + 1, buf ^ 1);
-    tri_load8<ORBIT>(P, delta, kTriRows * (s + 1 + kTriAhead) + 8 * sg, cc, n, y);
+    src.load8(kTriRows * (s + 1 + kTriAhead) + 8 * sg, y);
+    __builtin_amdgcn_sched_barrier(0);
   };
   // (whole groups of kTriAhead stages, the last ones of zeros: no branch between them)
   for (int s = 0; s < ns; s += kTriAhead) {
@@ -932,8 +965,15 @@ __global__ __launch_bounds__(kTriThreads, 4) void form_tri_kernel(const FormPara
     const float* const delta =
         P.delta + (int64_t)c * P.delta_s[0] + (int64_t)l * P.delta_s[1] + (int64_t)h * P.delta_s[2];
     uint16_t* const Tb = reinterpret_cast<uint16_t*>(Z);
-    if (P.n_orbit > 1) tri_gram<NB, true>(P, delta, J, Tb, acc);
-    else tri_gram<NB, false>(P, delta, J, Tb, acc);
+    const int sc = tid & 127;
+    if (P.n_orbit == 1 && P.unit_bytes > 0) {
+      const TriRows src = {__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(delta), (short)0, P.unit_bytes, 0x00020000),
+                           sc < d ? 4u * (uint32_t)sc : 0x7ffffff0u, 4 * (int32_t)P.delta_s[3], P.unit_bytes};
+      tri_gram<NB, true>(src, P.n_tokens, d, J, Tb, acc);
+    } else {
+      const TriOrbit src = {P, delta, (uint32_t)min(sc, d - 1)};
+      tri_gram<NB, false>(src, P.n_tokens, d, J, Tb, acc);
+    }
   }
   tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta, s_v0);
   __syncthreads();

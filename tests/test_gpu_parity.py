@@ -742,6 +742,37 @@ def test_form_patch_block_edges(device, units, n, d, m, w_odd):
         _check_patch(delta[0, 0, u], Ub[0, 0, u], Wb[0, 0, u][:, :d], sg[0, 0, u], m, (u,))
 
 
+@pytest.mark.parametrize("n,d,m,wide", [(40, 32, 1, 0), (33, 100, 8, 128), (130, 128, 16, 132), (31, 4, 2, 8)])
+def test_form_patch_row_strides(device, n, d, m, wide):
+    """Deficit rows as the loads see them: one row shared by every token (stride
+    0, the general form of the Gram loads), and rows inside wider ones, whose
+    further columns must not enter (they hold large values)."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch row strides n{n} d{d} m{m} wide{wide}", flush=True)
+    rng = np.random.default_rng(n + d)
+    if wide:
+        full = np.full((1, 1, 4, n, wide), 1e3, np.float32)
+        for u in range(4):
+            A = np.linalg.qr(rng.standard_normal((n, m)))[0]
+            B = np.linalg.qr(rng.standard_normal((d, m)))[0]
+            full[0, 0, u, :, :d] = (A * np.linspace(10.0, 2.0, m)) @ B.T + 0.01 * rng.standard_normal((n, d))
+        dt = torch.from_numpy(full).to(device)[..., :d]
+    else:
+        full = rng.standard_normal((1, 1, 4, 1, d)).astype(np.float32)
+        dt = torch.from_numpy(full).to(device).expand(1, 1, 4, n, d)
+        full = np.broadcast_to(full, (1, 1, 4, n, d))
+    U = torch.zeros((1, 1, 4, n, m), dtype=torch.bfloat16, device=device)
+    W = torch.zeros((1, 1, 4, m, d), dtype=torch.bfloat16, device=device)
+    sigma = torch.zeros((1, 1, 4, m), dtype=torch.float32, device=device)
+    km.form_patch(dt, U, W, sigma=sigma)
+    torch.cuda.synchronize()
+    Ub, Wb, sg = bits(U), bits(W), sigma.cpu().numpy()
+    for u in range(4):
+        _check_patch(full[0, 0, u, :, :d], Ub[0, 0, u], Wb[0, 0, u], sg[0, 0, u], m, (u,))
+
+
 @pytest.mark.parametrize("sweeps", [0, 12])
 def test_form_patch_degenerate_spectra(device, sweeps):
     """Spectra where the eigensolvers meet multiple or zero eigenvalues:
