@@ -793,7 +793,7 @@ static int build_form(const kamera_form_args* a, kamera::FormParams& P, bool& la
   {
     const __int128 row = a->delta_stride[3];
     const __int128 bytes = ((a->n_tokens - 1) * row + a->dim) * 4;
-    P.unit_bytes = row >= a->dim && ((__int128)a->n_tokens + 128) * row * 4 < 0x7ffffff0 ? (int32_t)bytes : 0;
+    P.unit_bytes = row >= a->dim && ((__int128)a->n_tokens + 512) * row * 4 < 0x7ffffff0 ? (int32_t)bytes : 0;
   }
   {
     bool wv = reinterpret_cast<uintptr_t>(a->W) % 16 == 0, up = reinterpret_cast<uintptr_t>(a->U) % 4 == 0;

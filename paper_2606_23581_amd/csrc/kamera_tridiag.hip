@@ -426,27 +426,31 @@ struct TriOrbit {
 // 128 (61 us with 32-row stages loaded one ahead): one wave per SIMD issues the
 // split (13 us), the products (13) and the waits for LDS and memory in turn;
 // with four units on the CU they overlap.
+// With S groups of four waves (form_tri_kernel) group g takes stages S s + g
+// into its own buffers and sums.
 constexpr int kTriAhead = 3;
+constexpr int kTriGramBytes = 2 * 3 * 128 * kTriRows * 2;   // a group's two staged buffers
 
-template <int NB, bool ZEROS, typename SRC>
-__device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, uint16_t* Tb, f32x16v (&acc)[NB]) {
+template <int NB, int S, bool ZEROS, typename SRC>
+__device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, int g, uint16_t* Tb, f32x16v (&acc)[NB]) {
   constexpr int kPart = 32 * NB * kTriRows;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int sc = tid & 127, sg = __builtin_amdgcn_readfirstlane(tid >> 7);
+  const int sc = tid & 127, sg = __builtin_amdgcn_readfirstlane(tid >> 7) & 1;
+  auto row0 = [&](int s) { return kTriRows * (S * s + g); };   // first row of the group's stage s
   const bool cin = sc < d;
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[I][r] = 0.f;
-  const int ns = (n + kTriRows - 1) / kTriRows;
+  const int ns = (n + kTriRows * S - 1) / (kTriRows * S);
   float x[kTriAhead][8];
 #pragma unroll
-  for (int a = 0; a < kTriAhead; ++a) src.load8(kTriRows * a + 8 * sg, x[a]);
+  for (int a = 0; a < kTriAhead; ++a) src.load8(row0(a) + 8 * sg, x[a]);
   uint16_t* const mine = Tb + tri_slot(sc, sg);
   auto put = [&](float (&y)[8], int s, int buf) {
-    if (!ZEROS && (kTriRows * (s + 1) > n || 32 * NB > d)) {   // zeros past n rows or d columns
+    if (!ZEROS && (row0(s) + kTriRows > n || 32 * NB > d)) {   // zeros past n rows or d columns
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] = kTriRows * s + 8 * sg + e < n && cin ? y[e] : 0.f;
+      for (int e = 0; e < 8; ++e) y[e] = row0(s) + 8 * sg + e < n && cin ? y[e] : 0.f;
     }
     u32x4v hi, mid, lo;
     split3_bf16x8(y, hi, mid, lo);
@@ -458,7 +462,7 @@ __device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, ui
     }
   };
   put(x[0], 0, 0);
-  src.load8(kTriRows * kTriAhead + 8 * sg, x[0]);
+  src.load8(row0(kTriAhead) + 8 * sg, x[0]);
   // stage s: y holds stage s + 1, split into the other buffer between the
   // products (past the last stage: zeros, never read), then takes the loads of stage s + 1 + kTriAhead.  The buffer it writes was
   // read in stage s - 1, before the barrier.
@@ -494,7 +498,7 @@ __device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, ui
       }
     }
     if (NB < 4) put(y, s + 1, buf ^ 1);
-    src.load8(kTriRows * (s + 1 + kTriAhead) + 8 * sg, y);
+    src.load8(row0(s + 1 + kTriAhead) + 8 * sg, y);
     __builtin_amdgcn_sched_barrier(0);
   };
   // (whole groups of kTriAhead stages, the last ones of zeros: no branch between them)
@@ -930,10 +934,50 @@ __device__ __forceinline__ void tri_apply(const float* V, const float* T, f32x4v
 
 extern __shared__ __align__(16) float tri_lds[];
 
-// zgroups: groups of 32 columns in the Z area; twice those of m let two lanes
+// Sums the groups' tiles into group 0, in the groups' order, two tiles at a time
+// through X: S - 1 groups x 2 tiles x 4 x 256 lanes of 16 bytes.
+template <int NB, int S>
+__device__ __forceinline__ void tri_gram_sum(f32x16v (&acc)[NB], int g, float* X) {
+  static_assert((S - 1) * 2 * 4 * kTriThreads * 16 <= S * kTriGramBytes, "the sums fit the staged buffers");
+  const int t = threadIdx.x & (kTriThreads - 1);
+#pragma unroll
+  for (int I0 = 0; I0 < NB; I0 += 2) {
+    __syncthreads();                           // the staged tiles, or the pair before, are read
+    if (g > 0) {
+      float* const x = X + ((g - 1) * 8 * kTriThreads + t) * 4;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (I0 + (q >> 2) < NB) {
+          const f32x16v& v = acc[I0 + (q >> 2)];
+          const int r = 4 * (q & 3);
+          *reinterpret_cast<f32x4v*>(x + q * kTriThreads * 4) = (f32x4v){v[r], v[r + 1], v[r + 2], v[r + 3]};
+        }
+    }
+    __syncthreads();
+    if (g == 0) {
+#pragma unroll
+      for (int o = 0; o < S - 1; ++o)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (I0 + (q >> 2) < NB) {
+            const f32x4v y = ld4(X + ((o * 8 + q) * kTriThreads + t) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[I0 + (q >> 2)][4 * (q & 3) + e] += y[e];
+          }
+    }
+  }
+}
+
+// S groups of four waves form G, each from its share of the token rows; the
+// first goes on alone.  A unit alone on its CU leaves the Gram stages to four
+// waves' chains of waits otherwise (more units on it fill each other's), and at
+// S = 2 a wave may hold 256 registers: 170, where 128 spill 156 values.  Eight
+// units of 1024 x 128, rank 64: 206 us a launch with S = 1, 190 with 2, 198
+// with 4 (128 registers again).
+// P.z_groups: groups of 32 columns in the Z area; twice those of m let two lanes
 // take an eigenvector
-template <int NB>
-__global__ __launch_bounds__(kTriThreads, 4) void form_tri_kernel(const FormParams /*by value, read in place*/) {
+template <int NB, int S>
+__global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kernel(const FormParams /*by value, read in place*/) {
   const FormParams& P = *static_cast<const FormParams*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
   const int unit = blockIdx.x;
   const int h = unit % P.n_heads;
@@ -946,6 +990,7 @@ __global__ __launch_bounds__(kTriThreads, 4) void form_tri_kernel(const FormPara
   // longest in the reduction, and the units that share a CU should not put
   // them on the same SIMD.
   const int J = (wave + (unit >> 3) + (unit >> 8)) & 3;
+  const int group = wave >> 2;                 // (0 where S is 1)
   float* const Z = tri_lds;
   float* const sv = Z + P.z_groups * kZGroup;
   float* const s_a = sv;                       // T's diagonal
@@ -964,15 +1009,20 @@ __global__ __launch_bounds__(kTriThreads, 4) void form_tri_kernel(const FormPara
   {
     const float* const delta =
         P.delta + (int64_t)c * P.delta_s[0] + (int64_t)l * P.delta_s[1] + (int64_t)h * P.delta_s[2];
-    uint16_t* const Tb = reinterpret_cast<uint16_t*>(Z);
+    uint16_t* const Tb = reinterpret_cast<uint16_t*>(Z) + (S > 1 ? group * (kTriGramBytes / 2) : 0);
+    const int g = S > 1 ? group : 0;
     const int sc = tid & 127;
     if (P.n_orbit == 1 && P.unit_bytes > 0) {
       const TriRows src = {__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(delta), (short)0, P.unit_bytes, 0x00020000),
                            sc < d ? 4u * (uint32_t)sc : 0x7ffffff0u, 4 * (int32_t)P.delta_s[3], P.unit_bytes};
-      tri_gram<NB, true>(src, P.n_tokens, d, J, Tb, acc);
+      tri_gram<NB, S, true>(src, P.n_tokens, d, J, g, Tb, acc);
     } else {
       const TriOrbit src = {P, delta, (uint32_t)min(sc, d - 1)};
-      tri_gram<NB, false>(src, P.n_tokens, d, J, Tb, acc);
+      tri_gram<NB, S, false>(src, P.n_tokens, d, J, g, Tb, acc);
+    }
+    if constexpr (S > 1) {
+      tri_gram_sum<NB, S>(acc, g, Z);
+      if (g > 0) return;                       // (a barrier waits for the waves that are left)
     }
   }
   tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta, s_v0);
@@ -1210,30 +1260,37 @@ __global__ __launch_bounds__(kTriThreads, 4) void form_tri_kernel(const FormPara
   if (P.sweeps_done != nullptr && tid == 0) P.sweeps_done[unit] = 0;
 }
 
-template <int NB>
+template <int NB, int S>
 hipError_t launch_tri(const FormParams& p, hipStream_t s) {
   static std::atomic<bool> lds_set[kMaxDevices];
-  const hipError_t e = ensure_lds_limit((const void*)form_tri_kernel<NB>, 4 * tri_lds_floats(6), lds_set);
+  const hipError_t e = ensure_lds_limit((const void*)form_tri_kernel<NB, S>, 4 * tri_lds_floats(6), lds_set);
   if (e != hipSuccess) return e;
+  static_assert(S * kTriGramBytes <= 6 * kZGroup * 4, "the groups' Gram buffers fit Z");
   FormParams q = p;
   // Z: the groups m needs, at least two (the Gram stage).  Launches of at most
   // two units per CU can afford twice that at m > 32: two lanes per vector.
   const int ng = (p.m + 31) / 32;
   // m > 64 needs two more for the staged reflectors.
-  q.z_groups = ng < 2 ? 2 : ng > 2 ? ng + 2 : (p.n_units <= 512 ? 4 : 2);
-  hipLaunchKernelGGL((form_tri_kernel<NB>), dim3((uint32_t)p.n_units), dim3(kTriThreads), 4 * tri_lds_floats(q.z_groups),
-                     s, q);
+  q.z_groups = S > 1 ? 6 : ng < 2 ? 2 : ng > 2 ? ng + 2 : (p.n_units <= 512 ? 4 : 2);
+  hipLaunchKernelGGL((form_tri_kernel<NB, S>), dim3((uint32_t)p.n_units), dim3(kTriThreads * S),
+                     4 * tri_lds_floats(q.z_groups), s, q);
   return hipGetLastError();
 }
 
 }  // namespace
 
+// The Gram stages are split where each unit has a CU to itself (256 of them)
+// and enough rows to pay for the sum.
+constexpr int kTriSplitUnits = 256;
+constexpr int kTriSplitRows = 128;
+
 hipError_t launch_form_tridiag(const FormParams& p, hipStream_t s) {
   switch ((p.dim + 31) / 32) {
-    case 1: return launch_tri<1>(p, s);
-    case 2: return launch_tri<2>(p, s);
-    case 3: return launch_tri<3>(p, s);
-    default: return launch_tri<4>(p, s);
+    case 1: return launch_tri<1, 1>(p, s);
+    case 2: return launch_tri<2, 1>(p, s);
+    case 3: return launch_tri<3, 1>(p, s);
+    default:
+      return p.n_units <= kTriSplitUnits && p.n_tokens >= kTriSplitRows ? launch_tri<4, 2>(p, s) : launch_tri<4, 1>(p, s);
   }
 }
 

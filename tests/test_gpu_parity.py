@@ -712,12 +712,16 @@ def test_form_patch_matches_svd(device, n, d, m):
 
 @pytest.mark.parametrize("units,n,d,m,w_odd", [(8, 33, 128, 32, False), (8, 129, 128, 33, True),
                                                (520, 48, 128, 40, False), (8, 200, 100, 65, True),
-                                               (8, 47, 68, 34, False), (8, 16, 8, 8, True)])
+                                               (8, 47, 68, 34, False), (8, 16, 8, 8, True),
+                                               (8, 127, 128, 16, False), (256, 128, 128, 64, False),
+                                               (257, 128, 128, 64, False), (8, 145, 100, 128 - 32, True)])
 def test_form_patch_block_edges(device, units, n, d, m, w_odd):
     """The tridiagonal solver where its layout changes: column counts around its
     32-wide blocks, token counts around its 16-row stages, ranks around one and
     two groups of 32 vectors, launches of more than two units per CU (one lane
-    per vector instead of two), and W rows that are not 16-byte aligned."""
+    per vector instead of two), launches around one unit per CU and token counts
+    around the fewest whose Gram stages are split, and W rows that are not
+    16-byte aligned."""
     import paper_2606_23581_amd as km
     import torch
 
@@ -742,7 +746,8 @@ def test_form_patch_block_edges(device, units, n, d, m, w_odd):
         _check_patch(delta[0, 0, u], Ub[0, 0, u], Wb[0, 0, u][:, :d], sg[0, 0, u], m, (u,))
 
 
-@pytest.mark.parametrize("n,d,m,wide", [(40, 32, 1, 0), (33, 100, 8, 128), (130, 128, 16, 132), (31, 4, 2, 8)])
+@pytest.mark.parametrize("n,d,m,wide", [(40, 32, 1, 0), (33, 100, 8, 128), (130, 128, 16, 132), (31, 4, 2, 8),
+                                         (150, 128, 1, 0)])
 def test_form_patch_row_strides(device, n, d, m, wide):
     """Deficit rows as the loads see them: one row shared by every token (stride
     0, the general form of the Gram loads), and rows inside wider ones, whose
