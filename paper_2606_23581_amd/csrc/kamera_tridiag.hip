@@ -7,8 +7,9 @@
 // accumulators of 32x32 MFMA tiles: lane l, element r of tile I is row
 // 32 I + 8 (r / 4) + 4 (l / 32) + r % 4, column 32 J + l % 32.
 //   1. G at fp32 accuracy on bf16 MFMA (32x32x16): Delta split exactly into
-//      three bf16 parts, the six products above 2^-27 relative, straight into
-//      those accumulators.
+//      three bf16 parts h + m + l, the six products above 2^-27 relative,
+//      straight into those accumulators; where a unit has a CU to itself, four
+//      of them (tri_symmetrize).
 //   2. Householder reduction in the same registers (tri_reduce).
 //   3. Eigenvalues by multisection on Sturm counts, eigenvectors of T by
 //      twisted factorisation, close ones orthogonalised, checks.
@@ -51,6 +52,7 @@ constexpr int kTriVec = 12 * 128 + 16; // a, b, beta, v0, b2, b2s, lam, cs, r2[4
 constexpr int tri_lds_floats(int zgroups) { return zgroups * kZGroup + kTriVec; }
 static_assert(32 * (kVLd + 36) <= 2 * kZGroup, "a staged block of reflectors fits two groups of Z");
 static_assert(2 * 3 * 128 * kTriRows * 2 <= 2 * kZGroup * 4, "the staged Gram parts fit two groups of Z");
+static_assert(4 * 32 * 36 <= 2 * kZGroup, "a tile of each wave fits two groups of Z");
 
 __device__ __forceinline__ float* zcol(float* Z, int k) { return Z + (k >> 5) * kZGroup + (k & 31); }
 
@@ -472,29 +474,65 @@ __device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, in
     const uint16_t* const Ts = Tb + buf * 3 * kPart;
     const int p = lane >> 5, c = lane & 31;
     if (NB == 4 || J < NB) {
-      bf16x8v b[3];
+      if constexpr (S > 1) {
+        // B: m, then h, 2m and 2l.  Doubled by one up in the exponent (a zero becomes
+        // 2^-126, far below the rounding of any G that is not itself subnormal;
+        // infinities and NaN still reach G through h^T h and m^T m)
+        auto part = [&](int q, int I) { return *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * I + c, p)); };
+        auto twice = [](bf16x8v v) { return __builtin_bit_cast(bf16x8v, __builtin_bit_cast(u32x4v, v) + 0x00800080u); };
+        // the four tiles' chains of products alternate (a product waits about twice
+        // its own 32 cycles for the one before it in its chain): m m; h 2l, h 2m, h h,
+        // one part of A at a time
+        bf16x8v b[3];
+        b[1] = part(1, J);
 #pragma unroll
-      for (int q = 0; q < 3; ++q) b[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * J + c, p));
-      // the tiles in pairs, whose chains of products alternate (a product waits
-      // about twice its own 32 cycles for the one before it in its chain): lo hi;
-      // mid mid, mid hi; hi lo, hi mid, hi hi, one part of A at a time
-#pragma unroll
-      for (int I0 = 0; I0 < NB; I0 += 4) {
-#pragma unroll
-        for (int q = 2; q >= 0; --q) {
+        for (int I0 = 0; I0 < NB; I0 += 4) {
           bf16x8v av[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u)
-            if (I0 + u < NB)
-              av[u] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * (I0 + u) + c, p));
+            if (I0 + u < NB) {
+              av[u] = part(1, I0 + u);
+              acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[1], acc[I0 + u], 0, 0, 0);
+            }
+          b[1] = twice(b[1]);
+          b[2] = twice(part(2, J));
+          b[0] = part(0, J);
 #pragma unroll
-          for (int t = 2 - q; t >= 0; --t)
+          for (int u = 0; u < 4; ++u)
+            if (I0 + u < NB) av[u] = part(0, I0 + u);
+#pragma unroll
+          for (int t = 2; t >= 0; --t)
 #pragma unroll
             for (int u = 0; u < 4; ++u)
               if (I0 + u < NB)
                 acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[t], acc[I0 + u], 0, 0, 0);
+          if (I0 == 0 && NB == 4) put(y, s + 1, buf ^ 1);
         }
-        if (I0 == 0 && NB == 4) put(y, s + 1, buf ^ 1);
+      } else {
+        bf16x8v b[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) b[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * J + c, p));
+        // the tiles in pairs, whose chains of products alternate (a product waits
+        // about twice its own 32 cycles for the one before it in its chain): lo hi;
+        // mid mid, mid hi; hi lo, hi mid, hi hi, one part of A at a time
+#pragma unroll
+        for (int I0 = 0; I0 < NB; I0 += 4) {
+#pragma unroll
+          for (int q = 2; q >= 0; --q) {
+            bf16x8v av[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (I0 + u < NB)
+                av[u] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * (I0 + u) + c, p));
+#pragma unroll
+            for (int t = 2 - q; t >= 0; --t)
+#pragma unroll
+              for (int u = 0; u < 4; ++u)
+                if (I0 + u < NB)
+                  acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[t], acc[I0 + u], 0, 0, 0);
+          }
+          if (I0 == 0 && NB == 4) put(y, s + 1, buf ^ 1);
+        }
       }
     }
     if (NB < 4) put(y, s + 1, buf ^ 1);
@@ -968,6 +1006,70 @@ __device__ __forceinline__ void tri_gram_sum(f32x16v (&acc)[NB], int g, float* X
   }
 }
 
+// h^T m and m^T h are transposes of one another, as are h^T l and l^T h: with
+// X = m^T m + h^T 2l + h^T 2m + h^T h, G = (X + X^T) / 2, four products a tile
+// for six.  Eight units of 1024 x 128: Gram stages and sums 37 -> 28 us, the
+// launch 190 -> 179.  Not at S = 1, where 128 registers are just enough without:
+// the steps of the reduction then spilled (1280 units x 2 with U and the
+// recall: 1957 -> 2415 us).
+// In pass k wave J's tile (J ^ k, J) meets its transpose, the
+// tile that wave J ^ k holds as (J, J ^ k), through 32 x kXLd floats a wave
+// (written row by row, read back as 16-byte pieces of a column: no conflicts).
+constexpr int kXLd = 36;
+
+template <int NB>
+__device__ __forceinline__ void tri_symmetrize(f32x16v (&acc)[NB], int J, float* X) {
+  const int lane = threadIdx.x & 63, c = lane & 31, h4 = 4 * (lane >> 5);
+  float* const mine = X + J * 32 * kXLd;
+  // (the tile number is a constant from the start and stands in an empty asm at
+  // each end of its branch: branches that differ in nothing else are merged into
+  // one with a run-time index into acc, which then lives in scratch)
+  auto write = [&](auto ic, int k) {
+    constexpr int I = decltype(ic)::value;
+    if constexpr (I < NB) {
+      if (I == (J ^ k)) {
+        asm volatile("; tile %0" ::"n"(I));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[(8 * (r >> 2) + h4 + (r & 3)) * kXLd + c] = acc[I][r];
+        asm volatile("; tile %0" ::"n"(I));
+      }
+    }
+  };
+  auto meet = [&](auto ic, int k) {
+    constexpr int I = decltype(ic)::value;
+    if constexpr (I < NB) {
+      if (I == (J ^ k)) {
+        asm volatile("; tile %0" ::"n"(I));
+        const float* const o = X + I * 32 * kXLd + c * kXLd + h4;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4v y = ld4(o + 8 * g);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[I][4 * g + e] = 0.5f * (acc[I][4 * g + e] + y[e]);
+        }
+        asm volatile("; tile %0" ::"n"(I));
+      }
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < (NB > 2 ? 4 : NB); ++k) {
+    __syncthreads();                           // the staged tiles, or the pass before, are read
+    if (J < NB) {
+      write(IntC<0>{}, k);
+      write(IntC<1>{}, k);
+      write(IntC<2>{}, k);
+      write(IntC<3>{}, k);
+    }
+    __syncthreads();
+    if (J < NB) {
+      meet(IntC<0>{}, k);
+      meet(IntC<1>{}, k);
+      meet(IntC<2>{}, k);
+      meet(IntC<3>{}, k);
+    }
+  }
+}
+
 // S groups of four waves form G, each from its share of the token rows; the
 // first goes on alone.  A unit alone on its CU leaves the Gram stages to four
 // waves' chains of waits otherwise (more units on it fill each other's), and at
@@ -1023,6 +1125,7 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
     if constexpr (S > 1) {
       tri_gram_sum<NB, S>(acc, g, Z);
       if (g > 0) return;                       // (a barrier waits for the waves that are left)
+      tri_symmetrize<NB>(acc, J, Z);
     }
   }
   tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta, s_v0);
@@ -1265,13 +1368,13 @@ hipError_t launch_tri(const FormParams& p, hipStream_t s) {
   static std::atomic<bool> lds_set[kMaxDevices];
   const hipError_t e = ensure_lds_limit((const void*)form_tri_kernel<NB, S>, 4 * tri_lds_floats(6), lds_set);
   if (e != hipSuccess) return e;
-  static_assert(S * kTriGramBytes <= 6 * kZGroup * 4, "the groups' Gram buffers fit Z");
+  static_assert(S == 1 || S * kTriGramBytes <= 4 * kZGroup * 4, "the groups' Gram buffers fit Z");
   FormParams q = p;
   // Z: the groups m needs, at least two (the Gram stage).  Launches of at most
   // two units per CU can afford twice that at m > 32: two lanes per vector.
   const int ng = (p.m + 31) / 32;
   // m > 64 needs two more for the staged reflectors.
-  q.z_groups = S > 1 ? 6 : ng < 2 ? 2 : ng > 2 ? ng + 2 : (p.n_units <= 512 ? 4 : 2);
+  q.z_groups = ng > 2 ? ng + 2 : S > 1 ? 4 : ng < 2 ? 2 : (p.n_units <= 512 ? 4 : 2);
   hipLaunchKernelGGL((form_tri_kernel<NB, S>), dim3((uint32_t)p.n_units), dim3(kTriThreads * S),
                      4 * tri_lds_floats(q.z_groups), s, q);
   return hipGetLastError();
