@@ -592,6 +592,15 @@ __device__ __forceinline__ void tri_scales(float x0, float sq, float& alpha, flo
   beta = sq != 0.f ? 2.f * __builtin_amdgcn_rcpf(fmaf(v0, v0, sq)) : 0.f;
 }
 
+// the same of a kept column, as the step decided (its v0)
+__device__ __forceinline__ void tri_scales_as(float step, float x0, float sq, float& alpha, float& v0, float& beta) {
+  const float nrm = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sq));
+  alpha = step != 0.f ? (step >= 0.f ? -nrm : nrm) : x0;
+  v0 = x0 - alpha;
+  const float den = fmaf(v0, v0, sq);
+  beta = step != 0.f && den != 0.f ? 2.f * __builtin_amdgcn_rcpf(den) : 0.f;
+}
+
 template <int V>
 struct IntC {
   static constexpr int value = V;
@@ -613,8 +622,8 @@ constexpr int kTriScr = 512 + 512;
 // inside the dependent chain (work for the matrix pipe, which issues in order
 // with it).
 template <int NB, typename F1, typename F2>
-__device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r1, float x0, float* vbuf, F1 mid1,
-                                            F2 mid2) {
+__device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r1, float x0, float* vbuf, float* s_v0,
+                                            int J, F1 mid1, F2 mid2) {
   const int lane = threadIdx.x & 63;
   const float q0 = lane > jn + 1 ? r0 : 0.f;
   const float q1 = lane + 64 > jn + 1 ? r1 : 0.f;
@@ -624,6 +633,7 @@ __device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r
   float v0, alpha;
   tri_scales(x0, sq, alpha, v0, S.beta);
   mid2();
+  if (J == NB - 1 && lane == 0) s_v0[jn] = S.beta != 0.f ? v0 : 0.f;   // (the wave that runs every step)
   S.v0 = lane == jn + 1 ? v0 : q0;
   vbuf[lane] = S.v0;
   if (NB > 2) {
@@ -635,7 +645,7 @@ __device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r
 // Steps 0 .. d - 3.  A wave runs those of its own and earlier blocks, then
 // clears its p in both buffers and only keeps the barriers.
 template <int NB>
-__device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, int d, float* scr) {
+__device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, int d, float* scr, float* s_v0) {
   const int lane = threadIdx.x & 63;
   const int col = 32 * J + (lane & 31);
   float* const vbuf = scr + 512 + 128 * J;
@@ -705,7 +715,7 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
     const float vj = tri_at(S.v0, S.v1, j + 1), wj = tri_at(w0, w1, j + 1);
     r0 = fmaf(-vj, w0, fmaf(-wj, S.v0, r0));
     if (NB > 2) r1 = fmaf(-vj, w1, fmaf(-wj, S.v1, r1));
-    tri_reflect<NB>(S, j + 1, r0, r1, tri_at(r0, r1, j + 2), vbuf, [&] { update(IntC<NB - 2>{}); },
+    tri_reflect<NB>(S, j + 1, r0, r1, tri_at(r0, r1, j + 2), vbuf, s_v0, J, [&] { update(IntC<NB - 2>{}); },
                     [&] { update(IntC<NB - 3>{}); });
     update(IntC<NB - 4>{});
   }
@@ -719,7 +729,11 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
 // in s_beta (zero past the last) and first entries in s_v0.  They are taken from
 // the columns as they are kept, after the steps (a step's own values are those
 // of the row, equal but for rounding): nothing but the chain is left in a step,
-// and V and beta agree to rounding however small x is.
+// and V and beta agree to rounding however small x is.  What a step decided
+// comes from the step, which left its v0 in s_v0: the sign (an x_0 within
+// rounding of zero may have the other sign in the column, and the reflector with
+// the other sign is another one: T would not be Q^T G Q, about one unit in 10^5)
+// and whether it reflected at all (v0 = 0: it did not).
 template <int NB>
 __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, float* scr, float* s_a, float* s_b,
                                            float* s_beta, float* s_v0) {
@@ -733,8 +747,9 @@ __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, flo
   if (J < NB && lane < 32) rb[32 * J + lane] = acc[0][0];
   __syncthreads();
   if (J < NB)
-    tri_reflect<NB>(S, 0, rb[lane], rb[64 + lane], lane_f(rb[lane], 1), scr + 512 + 128 * J, [] {}, [] {});
-  tri_steps<NB>(acc, S, J, d, scr);
+    tri_reflect<NB>(S, 0, rb[lane], rb[64 + lane], lane_f(rb[lane], 1), scr + 512 + 128 * J, s_v0, J, [] {}, [] {});
+  tri_steps<NB>(acc, S, J, d, scr, s_v0);
+  __syncthreads();                             // the last step's s_v0
   if (J < NB) {
     // column j of this lane: a_j = A[j][j], x_0 = A[j + 1][j], |x|^2 below it
     const int c = lane & 31, h4 = 4 * (lane >> 5), j = 32 * J + c;
@@ -756,7 +771,7 @@ __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, flo
     half_swap(x0, x02);
     half_swap(sq, sq2);
     float alpha, v0, beta;
-    tri_scales(x0 + x02, sq + sq2, alpha, v0, beta);
+    tri_scales_as(j < d - 2 ? s_v0[j] : 0.f, x0 + x02, sq + sq2, alpha, v0, beta);
     if (lane < 32 && j < d) {
       s_a[j] = aj + aj2;
       s_b[j] = alpha;                          // (column d - 2: sq = 0, alpha = A[d - 1][d - 2])

@@ -778,6 +778,50 @@ def test_form_patch_row_strides(device, n, d, m, wide):
         _check_patch(full[0, 0, u, :, :d], Ub[0, 0, u], Wb[0, 0, u], sg[0, 0, u], m, (u,))
 
 
+@pytest.mark.parametrize("units", [96, 288])
+def test_form_patch_zero_leading_entry(device, units):
+    """Deficits whose reflector of column `deep` starts from an entry that is zero
+    but for rounding: the sign that the reduction's step took for it has to be
+    the one that the back-transformation uses (the matrix is no longer symmetric
+    to the bit by then, so the row and the column may differ in it)."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    d, m, deep = 128, 32, 12
+    print(f"[case] form_patch zero leading entry units {units}", flush=True)
+    rng = np.random.default_rng(units)
+    delta = np.empty((1, 1, units, d, d), np.float32)
+    for u in range(units):
+        M = np.diag(rng.permutation(np.linspace(1.5, 9.0, d)))
+        N = np.triu(0.02 * rng.standard_normal((d, d)), 1)
+        N[:deep] = 0.0                           # tridiagonal down to column deep,
+        N[np.arange(deep), np.arange(1, deep + 1)] = 0.3
+        N[deep, deep + 1] = 0.0                  # which starts with a zero
+        M += N + N.T
+        # turned by reflectors that the steps before it undo: x_0 < 0, so alpha = +|x|
+        for k in reversed(range(1, deep + 1)):
+            v = rng.standard_normal(d)
+            v[:k] = 0.0
+            v[k] = 2.0 * np.linalg.norm(v[k + 1:])
+            M -= 2.0 * np.outer(v, v @ M) / (v @ v)
+            M -= 2.0 * np.outer(M @ v, v) / (v @ v)
+        M = 0.5 * (M + M.T)
+        delta[0, 0, u] = np.linalg.cholesky(M).T
+    U = torch.zeros((1, 1, units, d, m), dtype=torch.bfloat16, device=device)
+    W = torch.zeros((1, 1, units, m, d), dtype=torch.bfloat16, device=device)
+    sigma = torch.zeros((1, 1, units, m), dtype=torch.float32, device=device)
+    km.form_patch(torch.from_numpy(delta).to(device), U, W, sigma=sigma)
+    torch.cuda.synchronize()
+    Ub, Wb, sg = bits(U), bits(W), sigma.cpu().numpy()
+    for u in range(units):
+        # (the spectrum has no gap at m: the captured energy, not the product)
+        Wg, Dl = ref.bf16_to_f64(Wb[0, 0, u]), delta[0, 0, u].astype(np.float64)
+        S = np.linalg.svd(Dl, compute_uv=False)
+        assert np.max(np.abs(sg[0, 0, u] - S[:m]) / S[:m]) <= 1e-4, u
+        got = np.linalg.norm(Dl @ Wg.T, axis=0)
+        assert np.max(np.abs(got - S[:m]) / S[:m]) <= 2.0 ** -7, (u, np.max(np.abs(got - S[:m]) / S[:m]))
+
+
 @pytest.mark.parametrize("sweeps", [0, 12])
 def test_form_patch_degenerate_spectra(device, sweeps):
     """Spectra where the eigensolvers meet multiple or zero eigenvalues:
