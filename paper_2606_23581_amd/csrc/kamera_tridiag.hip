@@ -732,7 +732,7 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
 // and V and beta agree to rounding however small x is.  What a step decided
 // comes from the step, which left its v0 in s_v0: the sign (an x_0 within
 // rounding of zero may have the other sign in the column, and the reflector with
-// the other sign is another one: T would not be Q^T G Q, about one unit in 10^5)
+// the other sign is another one: T would not be Q^T G Q)
 // and whether it reflected at all (v0 = 0: it did not).
 template <int NB>
 __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, float* scr, float* s_a, float* s_b,
