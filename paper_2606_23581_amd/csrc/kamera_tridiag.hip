@@ -47,7 +47,7 @@ constexpr int kZLd = 33;
 constexpr int kZGroup = 128 * kZLd + 32;
 constexpr int kVLd = 132;              // staged reflector: 4-byte reads of 16 entries of 4 reflectors
                                        // (4 apart) fall on distinct banks
-constexpr int kTriVec = 12 * 128 + 16; // a, b, beta, v0, b2, b2s, lam, cs, r2[4]; lo, hi, fail
+constexpr int kTriVec = 11 * 128 + 16; // a, b, beta, b2, b2s, lam, cs, r2[4]; lo, hi, fail
 
 constexpr int tri_lds_floats(int zgroups) { return zgroups * kZGroup + kTriVec; }
 static_assert(32 * (kVLd + 36) <= 2 * kZGroup, "a staged block of reflectors fits two groups of Z");
@@ -579,9 +579,13 @@ __device__ __forceinline__ void half_swap(float& a, float& b) {
 // and its operands are lane-per-index vectors, a permlane32 swap each), and
 // while the matrix pipe runs forms the updated row j + 1 and the next
 // reflector, so nothing waits for an owner.
-// No column is touched once it is reduced (v and w are zero there), so column
-// j keeps x_j below the diagonal: the reflector v_j but for its first entry,
-// which goes to v0.  The back-transformation takes the reflectors from there.
+// No column is touched once it is reduced (v and w are zero there); after the
+// last step of its block its wave puts v_j in place of x_j, for the
+// back-transformation.  It has to be the step's own v: the matrix is symmetric to
+// rounding only (the six products of a tile and of its transpose are added in
+// different orders, as are the two outer products of an update), so where |x_j|
+// is itself rounding the column holds another vector than the row that v_j came
+// from, and a Q made of such vectors is not the one that T came from.
 // alpha, v's first entry and beta of the reflector of (x0, x) with |x|^2 = sq.
 // (hardware square root and reciprocal, 1 ulp each: beta is formed from the v
 // that is kept, so H is orthogonal to rounding; sq = 0: already reduced, H = I)
@@ -590,15 +594,6 @@ __device__ __forceinline__ void tri_scales(float x0, float sq, float& alpha, flo
   alpha = sq != 0.f ? (x0 >= 0.f ? -nrm : nrm) : x0;
   v0 = x0 - alpha;
   beta = sq != 0.f ? 2.f * __builtin_amdgcn_rcpf(fmaf(v0, v0, sq)) : 0.f;
-}
-
-// the same of a kept column, as the step decided (its v0)
-__device__ __forceinline__ void tri_scales_as(float step, float x0, float sq, float& alpha, float& v0, float& beta) {
-  const float nrm = __builtin_amdgcn_sqrtf(fmaf(x0, x0, sq));
-  alpha = step != 0.f ? (step >= 0.f ? -nrm : nrm) : x0;
-  v0 = x0 - alpha;
-  const float den = fmaf(v0, v0, sq);
-  beta = step != 0.f && den != 0.f ? 2.f * __builtin_amdgcn_rcpf(den) : 0.f;
 }
 
 template <int V>
@@ -614,16 +609,20 @@ struct TriVec {
 // entry i of a vector held as (lane, 64 + lane)
 __device__ __forceinline__ float tri_at(float x0, float x1, int i) { return lane_f(i < 64 ? x0 : x1, i & 63); }
 
-// scr: [2] x (p[128], row[128]) of alternate steps, then vbuf[4][128], a private copy of v per wave
-constexpr int kTriScr = 512 + 512;
+// scr: [2] x (p[128], row[128]) of alternate steps; the last 32 steps' v, written
+// by the wave that runs every step, in rows of kVLd; a copy of the last one for
+// each of the others, so that none waits for it
+constexpr int kTriScr = 512 + 32 * kVLd + 3 * 128;
+static_assert(kTriScr <= 2 * kZGroup, "the reduction's vectors fit two groups of Z");
 
 // The reflector of column jn <= d - 2 from its updated row (r0, r1), x0 =
-// row[jn + 1]; the wave's v_jn goes to its private vbuf.  mid1 and mid2 are run
+// row[jn + 1]; the wave's v_jn goes to its own vbuf, alpha and beta to s_b
+// and s_beta.  mid1 and mid2 are run
 // inside the dependent chain (work for the matrix pipe, which issues in order
 // with it).
 template <int NB, typename F1, typename F2>
-__device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r1, float x0, float* vbuf, float* s_v0,
-                                            int J, F1 mid1, F2 mid2) {
+__device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r1, float x0, float* vbuf, float* s_b,
+                                            float* s_beta, int J, F1 mid1, F2 mid2) {
   const int lane = threadIdx.x & 63;
   const float q0 = lane > jn + 1 ? r0 : 0.f;
   const float q1 = lane + 64 > jn + 1 ? r1 : 0.f;
@@ -633,7 +632,10 @@ __device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r
   float v0, alpha;
   tri_scales(x0, sq, alpha, v0, S.beta);
   mid2();
-  if (J == NB - 1 && lane == 0) s_v0[jn] = S.beta != 0.f ? v0 : 0.f;   // (the wave that runs every step)
+  if (J == NB - 1 && lane == 0) {              // (the wave that runs every step)
+    s_b[jn] = alpha;
+    s_beta[jn] = S.beta;
+  }
   S.v0 = lane == jn + 1 ? v0 : q0;
   vbuf[lane] = S.v0;
   if (NB > 2) {
@@ -645,15 +647,18 @@ __device__ __forceinline__ void tri_reflect(TriVec& S, int jn, float r0, float r
 // Steps 0 .. d - 3.  A wave runs those of its own and earlier blocks, then
 // clears its p in both buffers and only keeps the barriers.
 template <int NB>
-__device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, int d, float* scr, float* s_v0) {
+__device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, int d, float* scr, float* s_b,
+                                          float* s_beta) {
   const int lane = threadIdx.x & 63;
   const int col = 32 * J + (lane & 31);
-  float* const vbuf = scr + 512 + 128 * J;
-  const float* const vrow = vbuf + 4 * (lane >> 5);
+  float* const ring = scr + 512;
+  float* const vbase = J == NB - 1 ? ring : ring + 32 * kVLd + 128 * J;
+  const int vmask = J == NB - 1 ? 31 : 0;
   const int j_own = J < NB ? min(32 * J + 31, d - 2) : 0;
   for (int j = 0; j < j_own; ++j) {
     float* const pb = scr + 256 * (j & 1);
     const int ib = (j + 1) >> 5;               // first block of the trailing rows
+    const float* const vrow = vbase + kVLd * (j & vmask) + 4 * (lane >> 5);
     {
       float s[4] = {0.f, 0.f, 0.f, 0.f};
       // row j + 1 within its block: an element of one lane half, which writes
@@ -715,9 +720,29 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
     const float vj = tri_at(S.v0, S.v1, j + 1), wj = tri_at(w0, w1, j + 1);
     r0 = fmaf(-vj, w0, fmaf(-wj, S.v0, r0));
     if (NB > 2) r1 = fmaf(-vj, w1, fmaf(-wj, S.v1, r1));
-    tri_reflect<NB>(S, j + 1, r0, r1, tri_at(r0, r1, j + 2), vbuf, s_v0, J, [&] { update(IntC<NB - 2>{}); },
-                    [&] { update(IntC<NB - 3>{}); });
+    tri_reflect<NB>(S, j + 1, r0, r1, tri_at(r0, r1, j + 2), vbase + kVLd * ((j + 1) & vmask), s_b, s_beta,
+                    J, [&] { update(IntC<NB - 2>{}); }, [&] { update(IntC<NB - 3>{}); });
     update(IntC<NB - 4>{});
+  }
+  if (J < NB) {
+    // the reflectors into the wave's columns, below the diagonal, before the
+    // ring's rows are taken again (after the next barrier; the last of them is
+    // being written, so the wave reads its own copy of that)
+    const int c = lane & 31;
+    const float* const v = (c == 31 && J < NB - 1 ? vbase : ring + kVLd * c) + 4 * (lane >> 5);
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+      if (I >= J) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4v y = ld4(v + 32 * I + 8 * g);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = acc[I][4 * g + e];
+            acc[I][4 * g + e] = 32 * I + 8 * g + 4 * (lane >> 5) + e > col ? y[e] : x;
+          }
+        }
+      }
   }
   for (int j = j_own; j < d - 2; ++j) {
     if (J < NB && j < j_own + 2 && lane < 32) scr[256 * (j & 1) + col] = 0.f;
@@ -725,18 +750,11 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
   }
 }
 
-// Leaves T's diagonal and subdiagonal in s_a and s_b, the reflectors' scales
-// in s_beta (zero past the last) and first entries in s_v0.  They are taken from
-// the columns as they are kept, after the steps (a step's own values are those
-// of the row, equal but for rounding): nothing but the chain is left in a step,
-// and V and beta agree to rounding however small x is.  What a step decided
-// comes from the step, which left its v0 in s_v0: the sign (an x_0 within
-// rounding of zero may have the other sign in the column, and the reflector with
-// the other sign is another one: T would not be Q^T G Q)
-// and whether it reflected at all (v0 = 0: it did not).
+// Leaves T's diagonal and subdiagonal in s_a and s_b, the reflectors' scales in
+// s_beta (zero past the last) and the reflectors in acc's columns, below the diagonal.
 template <int NB>
 __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, float* scr, float* s_a, float* s_b,
-                                           float* s_beta, float* s_v0) {
+                                           float* s_beta) {
   const int lane = threadIdx.x & 63;
   TriVec S = {0.f, 0.f, 0.f};
   float* const rb = scr + 256 + 128;           // row 0 takes the buffer that step 0 does not
@@ -747,58 +765,41 @@ __device__ __forceinline__ void tri_reduce(f32x16v (&acc)[NB], int J, int d, flo
   if (J < NB && lane < 32) rb[32 * J + lane] = acc[0][0];
   __syncthreads();
   if (J < NB)
-    tri_reflect<NB>(S, 0, rb[lane], rb[64 + lane], lane_f(rb[lane], 1), scr + 512 + 128 * J, s_v0, J, [] {}, [] {});
-  tri_steps<NB>(acc, S, J, d, scr, s_v0);
-  __syncthreads();                             // the last step's s_v0
+    tri_reflect<NB>(S, 0, rb[lane], rb[64 + lane], lane_f(rb[lane], 1),
+                    scr + 512 + (J == NB - 1 ? 0 : 32 * kVLd + 128 * J), s_b, s_beta, J, [] {}, [] {});
+  tri_steps<NB>(acc, S, J, d, scr, s_b, s_beta);
+  __syncthreads();                             // the last step's vectors are read
   if (J < NB) {
-    // column j of this lane: a_j = A[j][j], x_0 = A[j + 1][j], |x|^2 below it
+    // a_j = A[j][j] of this lane's column
     const int c = lane & 31, h4 = 4 * (lane >> 5), j = 32 * J + c;
-    float aj = 0.f, x0 = 0.f, sq = 0.f;
+    float aj = 0.f;
 #pragma unroll
-    for (int I = 0; I < NB; ++I) {
-      if (I < J) continue;
+    for (int I = 0; I < NB; ++I)
+      if (I == J) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = 32 * I + 8 * (r >> 2) + (r & 3) + h4;
-        const float x = acc[I][r];
-        if (I == J) aj += i == j ? x : 0.f;
-        if (I == J || (I == J + 1 && r == 0)) x0 += i == j + 1 ? x : 0.f;
-        sq += i > j + 1 ? x * x : 0.f;
+        for (int r = 0; r < 16; ++r) aj += 8 * (r >> 2) + (r & 3) + h4 == c ? acc[I][r] : 0.f;
       }
-    }
-    float aj2 = aj, x02 = x0, sq2 = sq;
+    float aj2 = aj;
     half_swap(aj, aj2);
-    half_swap(x0, x02);
-    half_swap(sq, sq2);
-    float alpha, v0, beta;
-    tri_scales_as(j < d - 2 ? s_v0[j] : 0.f, x0 + x02, sq + sq2, alpha, v0, beta);
-    if (lane < 32 && j < d) {
-      s_a[j] = aj + aj2;
-      s_b[j] = alpha;                          // (column d - 2: sq = 0, alpha = A[d - 1][d - 2])
-      if (j < d - 2) s_beta[j] = beta;
-      s_v0[j] = v0;
-    }
+    if (lane < 32 && j < d) s_a[j] = aj + aj2;
   }
 }
 
 // ---- 2b. compact WY form of the reflectors ----
 // The 32 reflectors of block J multiply to I - V T V^T with
 // T^-1 = diag(1 / beta) + the strict upper triangle of S = V^T V.  Wave J
-// completes V in its tiles (first entries, zeros for columns past the last
-// reflector), takes S on MFMA (operand A and B are both the tile's own
-// registers) and solves for T's columns, one per lane.  -T goes into the
-// diagonal tile's rows i <= j, where V has no entries.
+// clears the columns past the last reflector, takes S on MFMA (operand A and B
+// are both the tile's own registers) and solves for T's columns, one per lane.
+// -T goes into the diagonal tile's rows i <= j, where V has no entries.
 // sw: 32 x kSLd floats private to the wave.
 constexpr int kSLd = 36;
 
 template <int NB>
-__device__ __forceinline__ void tri_wy(f32x16v (&acc)[NB], int J, int d, float* sw, const float* s_beta,
-                                       const float* s_v0) {
+__device__ __forceinline__ void tri_wy(f32x16v (&acc)[NB], int J, int d, float* sw, const float* s_beta) {
   if (J >= NB) return;
   const int lane = threadIdx.x & 63, c = lane & 31, h4 = 4 * (lane >> 5);
   const int j = 32 * J + c;                    // this lane's reflector
   const bool real = j < d - 2;
-  const float v0 = real ? s_v0[j] : 0.f;
   f32x16v S, diag;
 #pragma unroll
   for (int r = 0; r < 16; ++r) S[r] = diag[r] = 0.f;
@@ -809,13 +810,11 @@ __device__ __forceinline__ void tri_wy(f32x16v (&acc)[NB], int J, int d, float* 
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int f = 8 * (r >> 2) + (r & 3) + h4;
-        float x = f > c && real ? acc[I][r] : 0.f;
-        x = f == c + 1 ? v0 : x;
+        const float x = f > c && real ? acc[I][r] : 0.f;
         diag[r] = x;
         S = __builtin_amdgcn_mfma_f32_32x32x2f32(x, x, S, 0, 0, 0);
       }
     } else {
-      if (I == J + 1 && lane == 31) acc[I][0] = v0;   // reflector 32 J + 31 starts in this tile
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         acc[I][r] = real ? acc[I][r] : 0.f;
@@ -1113,13 +1112,12 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
   float* const s_a = sv;                       // T's diagonal
   float* const s_b = sv + 128;                 // T's subdiagonal
   float* const s_beta = sv + 2 * 128;          // reflector scales
-  float* const s_v0 = sv + 3 * 128;            // reflectors' first entries
-  float* const s_b2 = sv + 4 * 128;            // b_i^2
-  float* const s_b2s = sv + 5 * 128;           // b_{i-1}^2 (0 at i = 0)
-  float* const s_lam = sv + 6 * 128;           // eigenvalues, descending
-  int* const s_cs = reinterpret_cast<int*>(sv + 7 * 128);   // run start of each eigenvalue's cluster
-  float* const s_r2 = sv + 8 * 128;            // [4][128] partial sums
-  float* const s_misc = sv + 12 * 128;         // Gershgorin lo, hi
+  float* const s_b2 = sv + 3 * 128;            // b_i^2
+  float* const s_b2s = sv + 4 * 128;           // b_{i-1}^2 (0 at i = 0)
+  float* const s_lam = sv + 5 * 128;           // eigenvalues, descending
+  int* const s_cs = reinterpret_cast<int*>(sv + 6 * 128);   // run start of each eigenvalue's cluster
+  float* const s_r2 = sv + 7 * 128;            // [4][128] partial sums
+  float* const s_misc = sv + 11 * 128;         // Gershgorin lo, hi
   int* const s_fail = reinterpret_cast<int*>(s_misc + 2);
 
   f32x16v acc[NB];
@@ -1143,9 +1141,9 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
       tri_symmetrize<NB>(acc, J, Z);
     }
   }
-  tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta, s_v0);
+  tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta);
   __syncthreads();
-  tri_wy<NB>(acc, J, d, Z + kTriScr + 32 * kSLd * J, s_beta, s_v0);
+  tri_wy<NB>(acc, J, d, Z + 32 * kSLd * J, s_beta);
 
   // ---- 3. the m largest eigenpairs of T ----
   if (wave == 0) {                             // Gershgorin interval and b^2

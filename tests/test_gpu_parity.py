@@ -824,6 +824,60 @@ def test_form_patch_zero_leading_entry(device, units):
         assert res.max() <= 2.0 ** -7, (u, res.max())
 
 
+def _weakly_coupled_deficit(kind, n, d, m, rng):
+    """A deficit whose first channel couples to the others by rounding only, or
+    lies in an invariant subspace of two or three dimensions; gap at m."""
+    def ortho(r, c):
+        return np.linalg.qr(rng.standard_normal((r, c)))[0]
+
+    s = np.concatenate([np.linspace(10.0, 5.0, m), np.linspace(2.0, 1.0, d - m)])
+    if kind == "diagonal":                       # every channel orthogonal to every other
+        return ortho(n, d) * rng.permutation(s)
+    if kind == "folded":                         # [[a, B], [a, -B]]: the first one orthogonal to the others
+        a = ortho(n // 2, 1) * 4.0
+        B = ortho(n // 2, d - 1) * s[1:] @ ortho(d - 1, d - 1).T * 2.0 ** -0.5
+        return np.block([[a, B], [a, -B]])
+    k = int(kind[-1])                            # e_0 in the span of k right singular vectors, none of them the first
+    V = np.linalg.qr(np.column_stack([np.eye(d)[:, 0], rng.standard_normal((d, d - 1))]))[0]
+    V[:, :k] = V[:, :k] @ ortho(k, k)
+    V[:, k:] = V[:, k:] @ ortho(d - k, d - k)
+    return ortho(n, d) * np.concatenate([np.linspace(5.5, 5.0, k), np.linspace(10.0, 6.0, m - k), s[m:]]) @ V.T
+
+
+@pytest.mark.parametrize("kind", ["diagonal", "folded", "span2", "span3"])
+@pytest.mark.parametrize("units,n,d,m", [(8, 256, 128, 64), (288, 256, 128, 16), (8, 200, 96, 40), (8, 256, 64, 32),
+                                         (288, 64, 32, 8)])
+def test_form_patch_weakly_coupled_channel(device, kind, units, n, d, m):
+    """Deficits whose Gram matrix leaves the reduction a row that is rounding
+    alone while the rest of the matrix is large: the reflector that such a step
+    applies has to be the one that the back-transformation applies (the column
+    opposite the row holds other rounding).  Rows of W are eigenvectors of G to
+    their rounding: |G w - lambda w| <= |G - lambda| |dw| <= 2^-9 |G|, and 2^-12
+    for the 32-bit solve."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch weakly coupled {kind} units {units} n{n} d{d} m{m}", flush=True)
+    rng = np.random.default_rng(units + d)
+    some = np.stack([_weakly_coupled_deficit(kind, n, d, m, rng) for _ in range(16)]).astype(np.float32)
+    dt = torch.from_numpy(some).to(device)[torch.arange(units, device=device) % 16][None, None]
+    U = torch.zeros((1, 1, units, n, m), dtype=torch.bfloat16, device=device)
+    W = torch.zeros((1, 1, units, m, d), dtype=torch.bfloat16, device=device)
+    sigma = torch.zeros((1, 1, units, m), dtype=torch.float32, device=device)
+    km.form_patch(dt, U, W, sigma=sigma)
+    torch.cuda.synchronize()
+    Ub, Wb, sg = bits(U), bits(W), sigma.cpu().numpy()
+    worst = 0.0
+    for u in range(min(units, 16)):
+        Wg, Dl = ref.bf16_to_f64(Wb[0, 0, u]), some[u].astype(np.float64)
+        S = np.linalg.svd(Dl, compute_uv=False)
+        res = np.linalg.norm(Wg @ Dl.T @ Dl - S[:m, None] ** 2 * Wg, axis=1).max() / S[0] ** 2
+        worst = max(worst, res)
+    assert worst <= 2.0 ** -9 + 2.0 ** -12, worst
+    for u in range(0, min(units, 16), 5):
+        _check_patch(some[u], Ub[0, 0, u], Wb[0, 0, u], sg[0, 0, u], m, (u,))
+
+
 @pytest.mark.parametrize("sweeps", [0, 12])
 def test_form_patch_degenerate_spectra(device, sweeps):
     """Spectra where the eigensolvers meet multiple or zero eigenvalues:
