@@ -196,6 +196,17 @@ struct FormParams {
 
 size_t form_lds_bytes(int dim, int m);
 
+// Units that the tridiagonal solver leaves to Jacobi are formed by a grid of at
+// most kFormFallbackGrid workgroups; workgroup wg takes one unit of each row of
+// `grid` consecutive ones.  The degenerate units of a call lie in patterns -- a
+// layer or a head of every chunk -- so the place within a row moves from row to
+// row by Fibonacci hashing: with a plain remainder, layer 0 of 64 chunks of 32
+// layers x 8 heads came to 64 units on each of 8 workgroups.
+constexpr uint32_t kFormFallbackGrid = 256;
+constexpr uint32_t form_fallback_unit(uint32_t row, uint32_t wg, uint32_t grid) {
+  return row * grid + (grid == kFormFallbackGrid ? (wg + ((row * 2654435769u) >> 24)) % kFormFallbackGrid : wg);
+}
+
 // Raises a kernel's dynamic-LDS limit on the current device the first time it
 // is launched there.  `done` is the caller's per-device flag array (one per
 // kernel instantiation); two threads that race on a first launch both make

@@ -34,6 +34,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "kamera.h"
 #include "kamera_form.h"
 #include "kamera_launch.h"
@@ -601,10 +603,10 @@ __device__ __forceinline__ void jacobi_unit(const FormParams& P, int unit, int s
 }
 
 // FALLBACK = false: unit blockIdx.x, P.sweeps sweeps at most.  FALLBACK = true
-// (after form_tri_kernel): a workgroup looks at units blockIdx.x + k gridDim.x
-// and forms those whose W carries kFormFailMark.  Almost none does, so the
-// grid is small and a workgroup reads 1024 marks at once: the kernel then costs
-// its launch.
+// (after form_tri_kernel): a workgroup looks at its unit of every row of
+// gridDim.x units (form_fallback_unit) and forms those whose W carries
+// kFormFailMark.  Almost none does, so the grid is small and a workgroup reads
+// 1024 marks at once: the kernel then costs its launch.
 template <bool FALLBACK>
 __global__ __launch_bounds__(kFormThreads) void form_patch_kernel(const FormParams /*by value, read in place*/) {
   const FormParams& P = *static_cast<const FormParams*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
@@ -612,9 +614,9 @@ __global__ __launch_bounds__(kFormThreads) void form_patch_kernel(const FormPara
     jacobi_unit(P, blockIdx.x, P.sweeps);
   } else {
     __shared__ int s_todo;
-    const int64_t step = gridDim.x;
-    for (int64_t u0 = blockIdx.x; u0 < P.n_units; u0 += step * kFormThreads) {
-      const int64_t unit = u0 + step * threadIdx.x;
+    const uint32_t n_rows = ((uint32_t)P.n_units + gridDim.x - 1) / gridDim.x;   // (n_units < 2^22)
+    for (uint32_t row0 = 0; row0 < n_rows; row0 += kFormThreads) {
+      const int64_t unit = form_fallback_unit(row0 + threadIdx.x, blockIdx.x, gridDim.x);
       bool failed = false;
       if (unit < P.n_units) {
         const int64_t h = unit % P.n_heads, l = (unit / P.n_heads) % P.n_layers,
@@ -631,7 +633,7 @@ __global__ __launch_bounds__(kFormThreads) void form_patch_kernel(const FormPara
         const int t = s_todo;
         __syncthreads();                       // read before the next round resets it
         if (t >= kFormThreads) break;
-        jacobi_unit(P, (int)(u0 + step * t), kFormFallbackSweeps);
+        jacobi_unit(P, (int)form_fallback_unit(row0 + t, blockIdx.x, gridDim.x), kFormFallbackSweeps);
         from = t + 1;
       }
     }
@@ -823,7 +825,7 @@ hipError_t launch_form_patch(const FormParams& p, hipStream_t s) {
   } else {
     e = launch_form_tridiag(p, s);
     if (e != hipSuccess) return e;
-    e = launch_jacobi<true>(p, (uint32_t)(p.n_units < 256 ? p.n_units : 256), s);
+    e = launch_jacobi<true>(p, std::min((uint32_t)p.n_units, kFormFallbackGrid), s);
   }
   if (e != hipSuccess) return e;
   // U from the stored W, on the same stream: after the W of every unit

@@ -253,6 +253,39 @@ int main() {
     pt[4] = 8;
     CHECK(kamera_check_page_table(pt.data(), 2, 3, 48, 16, 8) == KAMERA_ERR_RANGE);
   }
+  // the units left to Jacobi: every unit has one workgroup, and the failures of
+  // one layer, one head or one (layer, head) of every chunk are spread over them
+  {
+    const uint32_t G = kamera::kFormFallbackGrid;
+    const int shapes[][3] = {{64, 32, 8}, {64, 64, 4}, {16, 64, 8}, {64, 80, 16}, {64, 28, 8}, {3, 40, 8}, {512, 16, 16}};
+    for (const auto& sh : shapes) {
+      const uint32_t C = sh[0], L = sh[1], H = sh[2], n = C * L * H;
+      std::vector<uint32_t> owner(n, G);
+      for (uint32_t row = 0; row * G < n; ++row)
+        for (uint32_t wg = 0; wg < G; ++wg) {
+          const uint32_t u = kamera::form_fallback_unit(row, wg, G);
+          if (u < n) {
+            CHECK(owner[u] == G);
+            owner[u] = wg;
+          }
+        }
+      for (int pattern = 0; pattern < 3; ++pattern) {
+        std::vector<uint32_t> load(G, 0);
+        uint32_t count = 0;
+        for (uint32_t u = 0; u < n; ++u) {
+          CHECK(owner[u] < G);
+          const bool layer0 = u / H % L == 0, head0 = u % H == 0;
+          if (pattern == 0 ? layer0 : pattern == 1 ? head0 : layer0 && head0) {
+            ++count;
+            ++load[owner[u]];
+          }
+        }
+        const uint32_t even = (count + G - 1) / G;
+        for (uint32_t wg = 0; wg < G; ++wg) CHECK(load[wg] <= 2 * even + 1);
+      }
+    }
+    for (uint32_t wg = 0; wg < 7; ++wg) CHECK(kamera::form_fallback_unit(0, wg, 7) == wg);
+  }
   // randomised structs on one thread, then on many at once
   fuzz(12345, 20000);
   {

@@ -934,6 +934,37 @@ def test_form_patch_degenerate_spectra(device, sweeps):
             assert np.max(np.abs(sg - S[:m]) / S[:m]) <= 1e-4, (name, sg[:4], S[:4])
 
 
+@pytest.mark.parametrize("C,L,H", [(5, 32, 8), (3, 9, 12), (1, 4, 2)])
+def test_form_patch_degenerate_layer(device, C, L, H):
+    """A layer whose deficits are zero in every chunk (it does not depend on the
+    context): its units, and only they, are formed by Jacobi, whichever
+    workgroup takes them."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch degenerate layer C{C} L{L} H{H}", flush=True)
+    n, d, m = 24, 32, 8
+    rng = np.random.default_rng(C * 100 + L)
+    A = np.linalg.qr(rng.standard_normal((C, L, H, n, m)))[0]
+    B = np.linalg.qr(rng.standard_normal((C, L, H, d, m)))[0]
+    delta = ((A * np.linspace(10.0, 2.0, m)) @ np.swapaxes(B, -1, -2)
+             + 0.01 * rng.standard_normal((C, L, H, n, d))).astype(np.float32)
+    delta[:, 1] = 0.0
+    U = torch.full((C, L, H, n, m), 7.0, dtype=torch.bfloat16, device=device)
+    W = torch.full((C, L, H, m, d), 7.0, dtype=torch.bfloat16, device=device)
+    sigma = torch.full((C, L, H, m), -1.0, dtype=torch.float32, device=device)
+    km.form_patch(torch.from_numpy(delta).to(device), U, W, sigma=sigma)
+    torch.cuda.synchronize()
+    Ub, Wb, sg = bits(U), bits(W), sigma.cpu().numpy()
+    for c, l, h in np.ndindex(C, L, H):
+        if l == 1:
+            Wg = ref.bf16_to_f64(Wb[c, l, h])
+            assert np.array_equal(Wg @ Wg.T, np.eye(m)), (c, h)
+            assert (Ub[c, l, h] == 0).all() and (sg[c, l, h] == 0).all(), (c, h)
+        elif (c + l + h) % 7 == 0:
+            _check_patch(delta[c, l, h], Ub[c, l, h], Wb[c, l, h], sg[c, l, h], m, (c, l, h))
+
+
 @pytest.mark.parametrize("K,n,d,m", [(3, 200, 128, 16), (6, 64, 64, 8), (1, 90, 128, 32)])
 def test_orbit_patch_matches_reference(device, K, n, d, m):
     """Orbit patch (Sec. 5, reorder): the K orderings' deficits share a
