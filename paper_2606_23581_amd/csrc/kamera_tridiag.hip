@@ -698,9 +698,11 @@ __device__ __forceinline__ void tri_steps(f32x16v (&acc)[NB], TriVec& S, int J, 
       p1 = pb[64 + lane];
       r1 = pb[192 + lane];
     }
-    const float pv = tri_wave_sum(NB > 2 ? fmaf(p0, S.v0, p1 * S.v1) : p0 * S.v0);
-    const float K = 0.5f * S.beta * S.beta * pv;
-    const float w0 = fmaf(-K, S.v0, S.beta * p0), w1 = fmaf(-K, S.v1, S.beta * p1);
+    // (beta p first: with |x| ~ g, beta is of the size of g^-2 and p^T v of g^3, and
+    // beta^2 or p^T v would leave the range of fp32 at g below 1e-9 or above 1e12)
+    const float q0 = S.beta * p0, q1 = S.beta * p1;
+    const float K = 0.5f * S.beta * tri_wave_sum(NB > 2 ? fmaf(q0, S.v0, q1 * S.v1) : q0 * S.v0);
+    const float w0 = fmaf(-K, S.v0, q0), w1 = fmaf(-K, S.v1, q1);
     // the update's operands: lanes < 32 v (w for B), others w (v), of a block
     float b0 = J >= 2 ? w1 : w0, b1 = J >= 2 ? S.v1 : S.v0;
     half_swap(b0, b1);

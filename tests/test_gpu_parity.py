@@ -934,6 +934,33 @@ def test_form_patch_degenerate_spectra(device, sweeps):
             assert np.max(np.abs(sg - S[:m]) / S[:m]) <= 1e-4, (name, sg[:4], S[:4])
 
 
+@pytest.mark.parametrize("scale", [1e-5, 1e-3, 1e4, 1e8])
+@pytest.mark.parametrize("units,n,d,m", [(4, 150, 128, 64), (4, 150, 32, 8), (288, 40, 128, 16)])
+def test_form_patch_scales(device, scale, units, n, d, m):
+    """Small and large deficits, the squares of whose Gram entries (at the noise's
+    level, too) are fp32 numbers: the tridiagonal solver forms them itself (no
+    Jacobi sweep)."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch scale {scale:g} units {units} n{n} d{d} m{m}", flush=True)
+    rng = np.random.default_rng(d + m)
+    A = np.linalg.qr(rng.standard_normal((units, n, m)))[0]
+    B = np.linalg.qr(rng.standard_normal((units, d, m)))[0]
+    delta = (((A * np.linspace(10.0, 2.0, m)) @ np.swapaxes(B, -1, -2) + 0.01 * rng.standard_normal((units, n, d)))
+             * scale).astype(np.float32)
+    U = torch.zeros((1, 1, units, n, m), dtype=torch.bfloat16, device=device)
+    W = torch.zeros((1, 1, units, m, d), dtype=torch.bfloat16, device=device)
+    sigma = torch.zeros((1, 1, units, m), dtype=torch.float32, device=device)
+    done = torch.full((1, 1, units), -1, dtype=torch.int32, device=device)
+    km.form_patch(torch.from_numpy(delta[None, None]).to(device), U, W, sigma=sigma, sweeps_done=done)
+    torch.cuda.synchronize()
+    Ub, Wb, sg = bits(U), bits(W), sigma.cpu().numpy()
+    for u in range(4):
+        _check_patch(delta[u], Ub[0, 0, u], Wb[0, 0, u], sg[0, 0, u], m, (u,))
+    assert (done == 0).all(), done.cpu().numpy()
+
+
 @pytest.mark.parametrize("C,L,H", [(5, 32, 8), (3, 9, 12), (1, 4, 2)])
 def test_form_patch_degenerate_layer(device, C, L, H):
     """A layer whose deficits are zero in every chunk (it does not depend on the
