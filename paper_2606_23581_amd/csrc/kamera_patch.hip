@@ -651,8 +651,8 @@ size_t form_lds_bytes(int dim, int /*m*/) {
 }
 
 // ---------------------------------------------------------------------------
-// U = Delta W^T, the factor's token side, from the W form_patch_kernel has
-// stored (so U W is formed from exactly the kept W).  A wave takes ROWS
+// U = Delta W^T, the factor's token side, from the W that the solver has stored
+// (so U W is formed from exactly the kept W).  A wave takes ROWS
 // token rows of one unit, as 16-row tiles, and the ranks 64 at a time (the
 // workgroup's four waves share those 64 W rows, staged once in LDS); the
 // products are 16x16x32 bf16 MFMAs with fp32 accumulation.  Delta is read in
@@ -664,7 +664,8 @@ size_t form_lds_bytes(int dim, int /*m*/) {
 // ---------------------------------------------------------------------------
 // token rows per wave: 64, so that the W rows a workgroup stages serve 256
 // token rows; 16 while the launch then has fewer than 512 workgroups (two per
-// CU) -- 8 units of 1024 rows: 15.5 us with 64, 6.4 with 16
+// CU).  Whole calls of 1024 rows, rank 64, with 16 and with 64: 8 units 200 and
+// 209 us, 100 units 214 and 216, 128 (512 workgroups) 217 and 217, 256 239 and 233
 constexpr int kURowsMany = 64, kURowsFew = 16;
 constexpr int kUThreads = 256;
 constexpr int kUWLd = 144;            // bf16 per staged W row: 288 bytes, so the B-operand reads

@@ -8,8 +8,8 @@
 // 32 I + 8 (r / 4) + 4 (l / 32) + r % 4, column 32 J + l % 32.
 //   1. G at fp32 accuracy on bf16 MFMA (32x32x16): Delta split exactly into
 //      three bf16 parts h + m + l, the six products above 2^-27 relative,
-//      straight into those accumulators; where a unit has a CU to itself, four
-//      of them (tri_symmetrize).
+//      straight into those accumulators; where a unit has a CU to itself, by
+//      two groups of four waves (S = 2).
 //   2. Householder reduction in the same registers (tri_reduce).
 //   3. Eigenvalues by multisection on Sturm counts, eigenvectors of T by
 //      twisted factorisation, close ones orthogonalised, checks.
@@ -52,7 +52,6 @@ constexpr int kTriVec = 11 * 128 + 16; // a, b, beta, b2, b2s, lam, cs, r2[4]; l
 constexpr int tri_lds_floats(int zgroups) { return zgroups * kZGroup + kTriVec; }
 static_assert(32 * (kVLd + 36) <= 2 * kZGroup, "a staged block of reflectors fits two groups of Z");
 static_assert(2 * 3 * 128 * kTriRows * 2 <= 2 * kZGroup * 4, "the staged Gram parts fit two groups of Z");
-static_assert(4 * 32 * 36 <= 2 * kZGroup, "a tile of each wave fits two groups of Z");
 
 __device__ __forceinline__ float* zcol(float* Z, int k) { return Z + (k >> 5) * kZGroup + (k & 31); }
 
@@ -141,7 +140,7 @@ __device__ __forceinline__ void twisted_vector(const float* __restrict__ a, cons
   // Every row of a visited group is stored: rows outside the pass get back
   // the value just read (D- below the twist, the vector above it), so the
   // steps are selects and not branches.
-  float nrm2 = 1.f, x = 1.f;
+  float up = 0.f, down = 0.f, x = 1.f;        // sums of squares (added as the two-lane form adds them)
   if (r > 0) {
     int g = (r - 1) >> 2;
     float qn[4];
@@ -164,7 +163,7 @@ __device__ __forceinline__ void twisted_vector(const float* __restrict__ a, cons
         const bool in = i < r;
         const float xn = -bc[u] * __builtin_amdgcn_rcpf(q[u] != 0.f ? q[u] : tiny) * x;
         x = in ? xn : x;
-        nrm2 += in ? xn * xn : 0.f;
+        up += in ? xn * xn : 0.f;
         z[i * ldz] = in ? xn : q[u];
       }
     }
@@ -197,12 +196,12 @@ __device__ __forceinline__ void twisted_vector(const float* __restrict__ a, cons
         const bool in = i > r;
         const float xn = -bb[u] * __builtin_amdgcn_rcpf(q[u] != 0.f ? q[u] : tiny) * x;
         x = in ? xn : x;
-        nrm2 += in ? xn * xn : 0.f;
+        down += in ? xn * xn : 0.f;
         z[i * ldz] = in ? xn : q[u];
       }
     }
   }
-  const float inv = 1.f / sqrtf(nrm2);
+  const float inv = 1.f / sqrtf(1.f + up + down);
   for (int g = 0; g < ng; ++g) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) z[(4 * g + u) * ldz] *= inv;
@@ -421,42 +420,45 @@ struct TriOrbit {
 
 // ---- 1. G = Delta^T Delta: tiles (I, J), I < NB, into acc ----
 // src: TriRows (ZEROS: it reads zeros past n rows or d columns) or TriOrbit.
-// Stages of kTriRows = 16 rows (one MFMA k-step) in two LDS buffers, one
+// Stages of S x kTriRows = 16 S rows (S MFMA k-steps) in two LDS buffers, one
 // barrier each: thread (sg, c) splits rows 8 sg .. 8 sg + 7 of column c of
 // stage s + 1 into three bf16 parts while stage s is multiplied; its loads are
-// issued kTriAhead stages before.  A unit alone on its CU takes 46 us for 1024 x
-// 128 (61 us with 32-row stages loaded one ahead): one wave per SIMD issues the
-// split (13 us), the products (13) and the waits for LDS and memory in turn;
-// with four units on the CU they overlap.
-// With S groups of four waves (form_tri_kernel) group g takes stages S s + g
-// into its own buffers and sums.
+// issued kTriAhead stages before.  One wave per SIMD issues the split, the
+// products and the waits for LDS and memory in turn; with four units on the CU
+// they overlap, and for a unit alone there S = 2 brings a second wave per SIMD:
+// group g of four waves forms tiles g NB / S .. (g + 1) NB / S - 1 of each column,
+// from all rows, so that a tile is the same sum in the same order whatever S is.
+// (With the rows split between the groups, and four products a tile for six by
+// adding the transpose, a call of 8 units of 1024 x 128 took 192 us for 200, but
+// a unit's patch then depended on how many shared its call.)
 constexpr int kTriAhead = 3;
-constexpr int kTriGramBytes = 2 * 3 * 128 * kTriRows * 2;   // a group's two staged buffers
+constexpr int kTriGramBytes = 2 * 3 * 128 * kTriRows * 2;   // two staged buffers of kTriRows rows
 
 template <int NB, int S, bool ZEROS, typename SRC>
-__device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, int g, uint16_t* Tb, f32x16v (&acc)[NB]) {
-  constexpr int kPart = 32 * NB * kTriRows;
+__device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, int g, uint16_t* Tb,
+                                         f32x16v (&acc)[NB / S]) {
+  constexpr int kPart = 32 * NB * kTriRows, NT = NB / S;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int sc = tid & 127, sg = __builtin_amdgcn_readfirstlane(tid >> 7) & 1;
-  auto row0 = [&](int s) { return kTriRows * (S * s + g); };   // first row of the group's stage s
+  const int sc = tid & 127, sg = __builtin_amdgcn_readfirstlane(tid >> 7) & (2 * S - 1);
+  auto row0 = [&](int s) { return kTriRows * S * s + 8 * sg; };   // first row of the thread's piece of stage s
   const bool cin = sc < d;
 #pragma unroll
-  for (int I = 0; I < NB; ++I)
+  for (int u = 0; u < NT; ++u)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[I][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[u][r] = 0.f;
   const int ns = (n + kTriRows * S - 1) / (kTriRows * S);
   float x[kTriAhead][8];
 #pragma unroll
-  for (int a = 0; a < kTriAhead; ++a) src.load8(row0(a) + 8 * sg, x[a]);
-  uint16_t* const mine = Tb + tri_slot(sc, sg);
+  for (int a = 0; a < kTriAhead; ++a) src.load8(row0(a), x[a]);
+  uint16_t* const mine = Tb + (sg >> 1) * 3 * kPart + tri_slot(sc, sg & 1);
   auto put = [&](float (&y)[8], int s, int buf) {
-    if (!ZEROS && (row0(s) + kTriRows > n || 32 * NB > d)) {   // zeros past n rows or d columns
+    if (!ZEROS && (kTriRows * S * (s + 1) > n || 32 * NB > d)) {   // zeros past n rows or d columns
 #pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] = row0(s) + 8 * sg + e < n && cin ? y[e] : 0.f;
+      for (int e = 0; e < 8; ++e) y[e] = row0(s) + e < n && cin ? y[e] : 0.f;
     }
     u32x4v hi, mid, lo;
     split3_bf16x8(y, hi, mid, lo);
-    uint16_t* q = mine + buf * 3 * kPart;
+    uint16_t* q = mine + buf * S * 3 * kPart;
     if (NB == 4 || sc < 32 * NB) {
       *reinterpret_cast<u32x4v*>(q) = hi;
       *reinterpret_cast<u32x4v*>(q + kPart) = mid;
@@ -464,79 +466,41 @@ __device__ __forceinline__ void tri_gram(const SRC& src, int n, int d, int J, in
     }
   };
   put(x[0], 0, 0);
-  src.load8(row0(kTriAhead) + 8 * sg, x[0]);
+  src.load8(row0(kTriAhead), x[0]);
   // stage s: y holds stage s + 1, split into the other buffer between the
-  // products (past the last stage: zeros, never read), then takes the loads of stage s + 1 + kTriAhead.  The buffer it writes was
-  // read in stage s - 1, before the barrier.
+  // products (past the last stage: zeros, never read), then takes the loads of
+  // stage s + 1 + kTriAhead.  The buffer it writes was read in stage s - 1, before
+  // the barrier.
   auto stage = [&](int s, float (&y)[8]) {
     const int buf = s & 1;
     __syncthreads();
-    const uint16_t* const Ts = Tb + buf * 3 * kPart;
     const int p = lane >> 5, c = lane & 31;
     if (NB == 4 || J < NB) {
-      if constexpr (S > 1) {
-        // B: m, then h, 2m and 2l.  Doubled by one up in the exponent (a zero becomes
-        // 2^-126, far below the rounding of any G that is not itself subnormal;
-        // infinities and NaN still reach G through h^T h and m^T m)
-        auto part = [&](int q, int I) { return *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * I + c, p)); };
-        auto twice = [](bf16x8v v) { return __builtin_bit_cast(bf16x8v, __builtin_bit_cast(u32x4v, v) + 0x00800080u); };
-        // the four tiles' chains of products alternate (a product waits about twice
-        // its own 32 cycles for the one before it in its chain): m m; h 2l, h 2m, h h,
-        // one part of A at a time
-        bf16x8v b[3];
-        b[1] = part(1, J);
 #pragma unroll
-        for (int I0 = 0; I0 < NB; I0 += 4) {
-          bf16x8v av[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (I0 + u < NB) {
-              av[u] = part(1, I0 + u);
-              acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[1], acc[I0 + u], 0, 0, 0);
-            }
-          b[1] = twice(b[1]);
-          b[2] = twice(part(2, J));
-          b[0] = part(0, J);
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (I0 + u < NB) av[u] = part(0, I0 + u);
-#pragma unroll
-          for (int t = 2; t >= 0; --t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (I0 + u < NB)
-                acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[t], acc[I0 + u], 0, 0, 0);
-          if (I0 == 0 && NB == 4) put(y, s + 1, buf ^ 1);
-        }
-      } else {
+      for (int k = 0; k < S; ++k) {
+        const uint16_t* const Ts = Tb + (buf * S + k) * 3 * kPart;
+        auto part = [&](int q, int col) { return *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(col + c, p)); };
         bf16x8v b[3];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) b[q] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * J + c, p));
-        // the tiles in pairs, whose chains of products alternate (a product waits
-        // about twice its own 32 cycles for the one before it in its chain): lo hi;
-        // mid mid, mid hi; hi lo, hi mid, hi hi, one part of A at a time
+        for (int q = 0; q < 3; ++q) b[q] = part(q, 32 * J);
+        // the tiles' chains of products alternate (a product waits about twice its
+        // own 32 cycles for the one before it in its chain): lo hi; mid mid, mid
+        // hi; hi lo, hi mid, hi hi, one part of A at a time
 #pragma unroll
-        for (int I0 = 0; I0 < NB; I0 += 4) {
+        for (int q = 2; q >= 0; --q) {
+          bf16x8v av[NT];
 #pragma unroll
-          for (int q = 2; q >= 0; --q) {
-            bf16x8v av[4];
+          for (int u = 0; u < NT; ++u) av[u] = part(q, 32 * (NT * g + u));
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (I0 + u < NB)
-                av[u] = *reinterpret_cast<const bf16x8v*>(Ts + q * kPart + tri_slot(32 * (I0 + u) + c, p));
+          for (int t = 2 - q; t >= 0; --t)
 #pragma unroll
-            for (int t = 2 - q; t >= 0; --t)
-#pragma unroll
-              for (int u = 0; u < 4; ++u)
-                if (I0 + u < NB)
-                  acc[I0 + u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[t], acc[I0 + u], 0, 0, 0);
-          }
-          if (I0 == 0 && NB == 4) put(y, s + 1, buf ^ 1);
+            for (int u = 0; u < NT; ++u) acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], b[t], acc[u], 0, 0, 0);
         }
+        if (k == 0 && NB == 4) put(y, s + 1, buf ^ 1);
       }
     }
     if (NB < 4) put(y, s + 1, buf ^ 1);
-    src.load8(row0(s + 1 + kTriAhead) + 8 * sg, y);
+    src.load8(row0(s + 1 + kTriAhead), y);
     __builtin_amdgcn_sched_barrier(0);
   };
   // (whole groups of kTriAhead stages, the last ones of zeros: no branch between them)
@@ -988,110 +952,41 @@ __device__ __forceinline__ void tri_apply(const float* V, const float* T, f32x4v
 
 extern __shared__ __align__(16) float tri_lds[];
 
-// Sums the groups' tiles into group 0, in the groups' order, two tiles at a time
-// through X: S - 1 groups x 2 tiles x 4 x 256 lanes of 16 bytes.
+// Brings the other groups' tiles to group 0, through X: (S - 1) NB / S tiles of
+// 4 x 256 lanes of 16 bytes.
 template <int NB, int S>
-__device__ __forceinline__ void tri_gram_sum(f32x16v (&acc)[NB], int g, float* X) {
-  static_assert((S - 1) * 2 * 4 * kTriThreads * 16 <= S * kTriGramBytes, "the sums fit the staged buffers");
+__device__ __forceinline__ void tri_gram_join(const f32x16v (&part)[NB / S], f32x16v (&acc)[NB], int g, float* X) {
+  constexpr int NT = NB / S;
   const int t = threadIdx.x & (kTriThreads - 1);
+  auto slot = [&](int I, int q) { return X + (((I - NT) * 4 + q) * kTriThreads + t) * 4; };
+  __syncthreads();                             // the staged tiles are read
+  if (g > 0) {
 #pragma unroll
-  for (int I0 = 0; I0 < NB; I0 += 2) {
-    __syncthreads();                           // the staged tiles, or the pair before, are read
-    if (g > 0) {
-      float* const x = X + ((g - 1) * 8 * kTriThreads + t) * 4;
+    for (int u = 0; u < NT; ++u)
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (I0 + (q >> 2) < NB) {
-          const f32x16v& v = acc[I0 + (q >> 2)];
-          const int r = 4 * (q & 3);
-          *reinterpret_cast<f32x4v*>(x + q * kTriThreads * 4) = (f32x4v){v[r], v[r + 1], v[r + 2], v[r + 3]};
-        }
-    }
-    __syncthreads();
-    if (g == 0) {
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4v*>(slot(NT * g + u, q)) =
+            (f32x4v){part[u][4 * q], part[u][4 * q + 1], part[u][4 * q + 2], part[u][4 * q + 3]};
+  }
+  __syncthreads();
+  if (g == 0) {
 #pragma unroll
-      for (int o = 0; o < S - 1; ++o)
+    for (int u = 0; u < NT; ++u) acc[u] = part[u];
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-          if (I0 + (q >> 2) < NB) {
-            const f32x4v y = ld4(X + ((o * 8 + q) * kTriThreads + t) * 4);
+    for (int I = NT; I < NB; ++I)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[I0 + (q >> 2)][4 * (q & 3) + e] += y[e];
-          }
-    }
+      for (int q = 0; q < 4; ++q) {
+        const f32x4v y = ld4(slot(I, q));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[I][4 * q + e] = y[e];
+      }
   }
 }
 
-// h^T m and m^T h are transposes of one another, as are h^T l and l^T h: with
-// X = m^T m + h^T 2l + h^T 2m + h^T h, G = (X + X^T) / 2, four products a tile
-// for six.  Eight units of 1024 x 128: Gram stages and sums 37 -> 28 us, the
-// launch 190 -> 179.  Not at S = 1, where 128 registers are just enough without:
-// the steps of the reduction then spilled (1280 units x 2 with U and the
-// recall: 1957 -> 2415 us).
-// In pass k wave J's tile (J ^ k, J) meets its transpose, the
-// tile that wave J ^ k holds as (J, J ^ k), through 32 x kXLd floats a wave
-// (written row by row, read back as 16-byte pieces of a column: no conflicts).
-constexpr int kXLd = 36;
-
-template <int NB>
-__device__ __forceinline__ void tri_symmetrize(f32x16v (&acc)[NB], int J, float* X) {
-  const int lane = threadIdx.x & 63, c = lane & 31, h4 = 4 * (lane >> 5);
-  float* const mine = X + J * 32 * kXLd;
-  // (the tile number is a constant from the start and stands in an empty asm at
-  // each end of its branch: branches that differ in nothing else are merged into
-  // one with a run-time index into acc, which then lives in scratch)
-  auto write = [&](auto ic, int k) {
-    constexpr int I = decltype(ic)::value;
-    if constexpr (I < NB) {
-      if (I == (J ^ k)) {
-        asm volatile("; tile %0" ::"n"(I));
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(8 * (r >> 2) + h4 + (r & 3)) * kXLd + c] = acc[I][r];
-        asm volatile("; tile %0" ::"n"(I));
-      }
-    }
-  };
-  auto meet = [&](auto ic, int k) {
-    constexpr int I = decltype(ic)::value;
-    if constexpr (I < NB) {
-      if (I == (J ^ k)) {
-        asm volatile("; tile %0" ::"n"(I));
-        const float* const o = X + I * 32 * kXLd + c * kXLd + h4;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4v y = ld4(o + 8 * g);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[I][4 * g + e] = 0.5f * (acc[I][4 * g + e] + y[e]);
-        }
-        asm volatile("; tile %0" ::"n"(I));
-      }
-    }
-  };
-#pragma unroll
-  for (int k = 0; k < (NB > 2 ? 4 : NB); ++k) {
-    __syncthreads();                           // the staged tiles, or the pass before, are read
-    if (J < NB) {
-      write(IntC<0>{}, k);
-      write(IntC<1>{}, k);
-      write(IntC<2>{}, k);
-      write(IntC<3>{}, k);
-    }
-    __syncthreads();
-    if (J < NB) {
-      meet(IntC<0>{}, k);
-      meet(IntC<1>{}, k);
-      meet(IntC<2>{}, k);
-      meet(IntC<3>{}, k);
-    }
-  }
-}
-
-// S groups of four waves form G, each from its share of the token rows; the
-// first goes on alone.  A unit alone on its CU leaves the Gram stages to four
-// waves' chains of waits otherwise (more units on it fill each other's), and at
-// S = 2 a wave may hold 256 registers: 170, where 128 spill 156 values.  Eight
-// units of 1024 x 128, rank 64: 206 us a launch with S = 1, 190 with 2, 198
-// with 4 (128 registers again).
+// S groups of four waves form G, each a share of the tiles; the first goes on
+// alone.  A unit alone on its CU leaves the Gram stages to four waves' chains of
+// waits otherwise (more units on it fill each other's), and at S = 2 a wave may
+// hold 256 registers: 168, where 128 spill 146 values.
 // P.z_groups: groups of 32 columns in the Z area; twice those of m let two lanes
 // take an eigenvector
 template <int NB, int S>
@@ -1126,21 +1021,24 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
   {
     const float* const delta =
         P.delta + (int64_t)c * P.delta_s[0] + (int64_t)l * P.delta_s[1] + (int64_t)h * P.delta_s[2];
-    uint16_t* const Tb = reinterpret_cast<uint16_t*>(Z) + (S > 1 ? group * (kTriGramBytes / 2) : 0);
+    uint16_t* const Tb = reinterpret_cast<uint16_t*>(Z);
     const int g = S > 1 ? group : 0;
     const int sc = tid & 127;
+    f32x16v part[NB / S];
     if (P.n_orbit == 1 && P.unit_bytes > 0) {
       const TriRows src = {__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(delta), (short)0, P.unit_bytes, 0x00020000),
                            sc < d ? 4u * (uint32_t)sc : 0x7ffffff0u, 4 * (int32_t)P.delta_s[3], P.unit_bytes};
-      tri_gram<NB, S, true>(src, P.n_tokens, d, J, g, Tb, acc);
+      tri_gram<NB, S, true>(src, P.n_tokens, d, J, g, Tb, part);
     } else {
       const TriOrbit src = {P, delta, (uint32_t)min(sc, d - 1)};
-      tri_gram<NB, S, false>(src, P.n_tokens, d, J, g, Tb, acc);
+      tri_gram<NB, S, false>(src, P.n_tokens, d, J, g, Tb, part);
     }
     if constexpr (S > 1) {
-      tri_gram_sum<NB, S>(acc, g, Z);
+      tri_gram_join<NB, S>(part, acc, g, Z);
       if (g > 0) return;                       // (a barrier waits for the waves that are left)
-      tri_symmetrize<NB>(acc, J, Z);
+    } else {
+#pragma unroll
+      for (int I = 0; I < NB; ++I) acc[I] = part[I];
     }
   }
   tri_reduce<NB>(acc, J, d, Z, s_a, s_b, s_beta);
@@ -1383,10 +1281,13 @@ hipError_t launch_tri(const FormParams& p, hipStream_t s) {
   static std::atomic<bool> lds_set[kMaxDevices];
   const hipError_t e = ensure_lds_limit((const void*)form_tri_kernel<NB, S>, 4 * tri_lds_floats(6), lds_set);
   if (e != hipSuccess) return e;
-  static_assert(S == 1 || S * kTriGramBytes <= 4 * kZGroup * 4, "the groups' Gram buffers fit Z");
+  static_assert(S == 1 || (S * kTriGramBytes <= 4 * kZGroup * 4 && (NB - NB / S) * 4096 * 4 <= 4 * kZGroup * 4),
+                "the Gram buffers, and the tiles handed over, fit Z");
   FormParams q = p;
   // Z: the groups m needs, at least two (the Gram stage).  Launches of at most
-  // two units per CU can afford twice that at m > 32: two lanes per vector.
+  // two units per CU can afford twice that at m > 32: two lanes per vector (calls
+  // of 264 units of 128 x 128, rank 64: 227 us with two groups, 218 with four; 512:
+  // 239 and 229; but 520, whose third unit on a CU then waits: 279 and 372).
   const int ng = (p.m + 31) / 32;
   // m > 64 needs two more for the staged reflectors.
   q.z_groups = ng > 2 ? ng + 2 : S > 1 ? 4 : ng < 2 ? 2 : (p.n_units <= 512 ? 4 : 2);
@@ -1397,10 +1298,11 @@ hipError_t launch_tri(const FormParams& p, hipStream_t s) {
 
 }  // namespace
 
-// The Gram stages are split where each unit has a CU to itself (256 of them)
-// and enough rows to pay for the sum.
+// The Gram stages are split where each unit has a CU to itself (256 of them), at
+// any number of rows (calls with S = 1 and 2, rank 64: 8 units of 1024 x 128 218 and
+// 200 us, of 64 x 128 175 and 170; 256 units of 1024 x 128 249 and 231, of 64 x 128
+// 180 and 173; rank 8, 256 units of 16 x 128 170 and 168).
 constexpr int kTriSplitUnits = 256;
-constexpr int kTriSplitRows = 128;
 
 hipError_t launch_form_tridiag(const FormParams& p, hipStream_t s) {
   switch ((p.dim + 31) / 32) {
@@ -1408,7 +1310,7 @@ hipError_t launch_form_tridiag(const FormParams& p, hipStream_t s) {
     case 2: return launch_tri<2, 1>(p, s);
     case 3: return launch_tri<3, 1>(p, s);
     default:
-      return p.n_units <= kTriSplitUnits && p.n_tokens >= kTriSplitRows ? launch_tri<4, 2>(p, s) : launch_tri<4, 1>(p, s);
+      return p.n_units <= kTriSplitUnits ? launch_tri<4, 2>(p, s) : launch_tri<4, 1>(p, s);
   }
 }
 

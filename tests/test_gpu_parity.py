@@ -719,9 +719,8 @@ def test_form_patch_block_edges(device, units, n, d, m, w_odd):
     """The tridiagonal solver where its layout changes: column counts around its
     32-wide blocks, token counts around its 16-row stages, ranks around one and
     two groups of 32 vectors, launches of more than two units per CU (one lane
-    per vector instead of two), launches around one unit per CU and token counts
-    around the fewest whose Gram stages are split, and W rows that are not
-    16-byte aligned."""
+    per vector instead of two), launches around one unit per CU, whose Gram
+    stages are split, and W rows that are not 16-byte aligned."""
     import paper_2606_23581_amd as km
     import torch
 
@@ -959,6 +958,37 @@ def test_form_patch_scales(device, scale, units, n, d, m):
     for u in range(4):
         _check_patch(delta[u], Ub[0, 0, u], Wb[0, 0, u], sg[0, 0, u], m, (u,))
     assert (done == 0).all(), done.cpu().numpy()
+
+
+@pytest.mark.parametrize("n,d,m,K", [(512, 128, 64, 1), (200, 128, 40, 1), (129, 100, 8, 1), (300, 128, 72, 1),
+                                     (150, 128, 33, 3), (90, 64, 64, 1), (47, 128, 16, 1)])
+def test_form_patch_does_not_depend_on_the_call(device, n, d, m, K):
+    """A unit's patch is the same, bit for bit, in a call of few units (whose Gram
+    stages are split), of more than 256 and of more than 512 (one lane per
+    vector), and whatever the strides of its rows (with and without a buffer
+    descriptor): a layer-wise compile gives what a whole-model one gives."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch call sizes n{n} d{d} m{m} K{K}", flush=True)
+    rng = np.random.default_rng(n + d + m)
+    basis = np.linalg.qr(rng.standard_normal((d, d)))[0]
+    few = (rng.standard_normal((K, 1, 1, 8, n, d)) * (1.0 + np.arange(d)) ** -0.25) @ basis
+    few[..., 7, :, 1:3] = few[..., 7, :, :1]     # a unit with a double zero eigenvalue
+    few = torch.from_numpy(few.astype(np.float32)).to(device)
+    want = None
+    for units in (8, 256, 264, 600):
+        dt = few[:, :, :, torch.arange(units, device=device) % 8]
+        U = torch.zeros((1, 1, units, n, m), dtype=torch.bfloat16, device=device)
+        W = torch.zeros((1, 1, units, m, d), dtype=torch.bfloat16, device=device)
+        sigma = torch.zeros((1, 1, units, m), dtype=torch.float32, device=device)
+        km.form_patch(dt if K > 1 else dt[0], U, W, sigma=sigma)
+        torch.cuda.synchronize()
+        got = [bits(U)[0, 0], bits(W)[0, 0], sigma.cpu().numpy()[0, 0]]
+        if want is None:
+            want = got
+        for x, y in zip(got, want):
+            assert np.array_equal(x, y[np.arange(units) % 8]), units
 
 
 @pytest.mark.parametrize("C,L,H", [(5, 32, 8), (3, 9, 12), (1, 4, 2)])
