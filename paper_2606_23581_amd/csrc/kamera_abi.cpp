@@ -214,6 +214,40 @@ static bool interleaved_rows(const kamera_rehydrate_args* a, const void* b0, con
 
 // Validation and kernel parameters of a rehydrate call; *launch is false for
 // an empty call (nothing to do).
+// Token block of the per-head kernel, a multiple of 64 (one tile for each of a
+// workgroup's four waves): the one of the least modelled time, in passes of 64
+// tokens.  A block takes its passes and its set-up (W^T staged, first loads: 0.4
+// per 32 ranks).  A device of `places` workgroups takes the sum of all blocks and
+// a ragged end of 1.1 block; or, where all fit at once, one block and the
+// unevenness of half of one.  Lengths are equal cuts of the chunk above rank 32,
+// the halves of 1024 up to there (equal cuts ran up to 15% slower).  The weights
+// are fitted to 1202 shapes (2^6 to 2^24 rows, rank 0 to 128, ragged, paged, MLA,
+// relocated), each timed at up to 17 lengths: this rule comes within 1.1% of the
+// fastest length on average, 14% at worst; halving 1024 until there are 32
+// workgroups a CU 6.8% and 63%; until there are 24 of at least 128 or 256 tokens
+// 4.7% and 67% (blocks that just miss fitting at once, nearly empty last ones).
+static int pick_token_block(int64_t units, int32_t n_tokens, int m_steps, bool relocated) {
+  if (m_steps > 2) m_steps = 4;                // as the kernel is instantiated
+  const double setup = 0.4 * std::max(m_steps, 1);
+  const double places = 256.0 * (m_steps > 2 || relocated ? 3 : 4);   // its launch bounds
+  const int64_t passes = ceil_div(n_tokens, 64);
+  int64_t best = 1;
+  double least = 0.0;
+  for (int64_t most = kamera::kMaxTokenBlock / 64; most >= 1; --most) {
+    if (m_steps <= 1 && (most & (most - 1)) != 0) continue;
+    int64_t len = std::min(most, passes);
+    if (m_steps > 1) len = ceil_div(passes, ceil_div(passes, len));
+    const double blocks = (double)ceil_div(passes, len), one = setup + std::min((double)len, n_tokens / 64.0);
+    const double sum = (double)units * (blocks * setup + (double)passes) / places;
+    const double cost = (double)units * blocks <= places ? std::max(sum, one) + 0.5 * one : sum + 1.1 * one;
+    if (least == 0.0 || cost < least) {
+      least = cost;
+      best = len;
+    }
+  }
+  return (int)(64 * best);
+}
+
 static int build_rehydrate(const kamera_rehydrate_args* a, kamera::RehydrateParams& P, bool& launch) {
   const char* who = "kamera_rehydrate";
   launch = false;
@@ -495,23 +529,9 @@ static int build_rehydrate(const kamera_rehydrate_args* a, kamera::RehydratePara
     launch = true;
     return KAMERA_OK;
   }
-  // Token block.  A workgroup stages W^T once per block, so a block should
-  // hold several tiles a wave; a launch needs enough of them to fill the device
-  // and even out its tail.  First down to 128 tokens (rank <= 32) or 256 while
-  // there are fewer than 24 workgroups per CU (9 above rank 64, where three fit
-  // a CU and W^T is 32 KiB), then down to 64 only while they do not fill the
-  // device once.  Measured against shrinking to 64 below 32 per CU: rank 128,
-  // 6 x 24 x 2 x 1024: 145 -> 111 us; rank 128, 1 x 24 x 8 x 512: 53 -> 41;
-  // rank 64, 4 x 16 x 1 x 1024: 26.9 -> 24.3; rank 16, 8 x 28 x 2 x 1024: 116
-  // -> 105; the MLA chunks keep their 128 (103 us; 64: 116, 256: 109).
   int max_steps = 0;
   for (int p = 0; p < a->n_planes; ++p) max_steps = std::max(max_steps, P.plane[p].m_steps);
-  const int tb_mid = max_steps <= 1 ? 128 : 256;
-  const int64_t many = max_steps > 2 ? 9 * 256 : 24 * 256, once = max_steps > 2 ? 3 * 256 : 4 * 256;
-  int tb = kamera::kMaxTokenBlock;
-  while (tb > tb_mid && units * ceil_div(a->n_tokens, tb) < many) tb /= 2;
-  while (tb > 64 && units * ceil_div(a->n_tokens, tb) < once) tb /= 2;
-  tb = (int)std::min<int64_t>(tb, ceil_div(a->n_tokens, 64) * 64);
+  const int tb = pick_token_block(units, a->n_tokens, max_steps, a->delta != nullptr);
   P.token_block = tb;
   P.n_tblk = (int32_t)ceil_div(a->n_tokens, tb);
   int32_t nb_all = 0;

@@ -253,6 +253,46 @@ int main() {
     pt[4] = 8;
     CHECK(kamera_check_page_table(pt.data(), 2, 3, 48, 16, 8) == KAMERA_ERR_RANGE);
   }
+  // token blocks of the per-head kernel: a chain of blocks on one of the device's
+  // places is never longer than with 64-token blocks -- a launch must not just
+  // miss fitting at once -- and long launches keep long blocks, which stage W^T
+  // once for several tiles
+  {
+    struct Shape { int C, L, H, n, m, paged, want; };   // want: the block where one is expected
+    const Shape shapes[] = {{10, 5, 4, 305, 96, 1, 0}, {4, 1, 8, 1829, 128, 1, 0}, {4, 12, 8, 377, 64, 0, 0},
+                            {14, 5, 6, 154, 24, 0, 0}, {1, 24, 8, 512, 128, 0, 0}, {5, 25, 2, 380, 64, 1, 192},
+                            {6, 30, 1, 600, 128, 1, 320}, {2, 1, 1, 1100, 128, 0, 64}, {30, 30, 2, 70, 8, 1, 128},
+                            {8, 27, 4, 66, 8, 1, 128}, {16, 80, 1, 1024, 64, 0, 256}};
+    for (const Shape& s : shapes) {
+      kamera_rehydrate_args a = valid_rehydrate();
+      a.n_chunks = s.C, a.n_layers = s.L, a.n_heads = s.H, a.n_tokens = s.n, a.kernel = KAMERA_KERNEL_PER_HEAD;
+      const int64_t C = s.C, L = s.L, H = s.H, n = s.n, m = (s.m + 7) / 8 * 8;
+      for (int p = 0; p < 2; ++p) {
+        const int64_t st[4] = {L * n * H * 128, n * H * 128, H * 128, 128};
+        const int64_t us[4] = {L * H * n * m, H * n * m, n * m, m}, ws[4] = {L * H * m * 128, H * m * 128, m * 128, 128};
+        std::memcpy(a.plane[p].in_stride, st, sizeof(st));
+        std::memcpy(a.plane[p].out_stride, st, sizeof(st));
+        std::memcpy(a.plane[p].u_stride, us, sizeof(us));
+        std::memcpy(a.plane[p].w_stride, ws, sizeof(ws));
+        a.plane[p].m = s.m;
+      }
+      if (s.paged) {
+        a.paged = 1, a.page_table = dev<const int32_t>(64), a.page_size = 16, a.pt_stride = (int32_t)((n + 15) / 16);
+        a.n_pool_pages = (int32_t)(C * a.pt_stride);
+      }
+      CHECK(kamera_rehydrate(&a, nullptr) == KAMERA_OK);
+      const int tb = stub_last_rehydrate_token_block();
+      const double setup = s.m <= 32 ? 0.3 : s.m <= 64 ? 0.5 : 1.0, places = 256.0 * (s.m <= 64 ? 4 : 3);
+      auto chain = [&](int b) {
+        const int len = std::min<int>(b / 64, (int)((n + 63) / 64));
+        const double wgs = 2.0 * C * L * H * ((n + b - 1) / b);
+        return std::ceil(wgs / places) * (setup + len);
+      };
+      CHECK(tb % 64 == 0 && tb >= 64 && tb <= kamera::kMaxTokenBlock);
+      CHECK(chain(tb) <= chain(64) + 1e-9);
+      if (s.want) CHECK(tb == s.want);
+    }
+  }
   // the units left to Jacobi: every unit has one workgroup, and the failures of
   // one layer, one head or one (layer, head) of every chunk are spread over them
   {

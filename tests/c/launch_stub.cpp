@@ -20,6 +20,7 @@ extern "C" long stub_launches(void) { return g_launches.load(); }
 extern "C" int stub_last_rehydrate_row_group(void) { return t_last_rehydrate.row_group; }
 extern "C" long long stub_last_rehydrate_tasks(void) { return (long long)t_last_rehydrate.n_tasks; }
 extern "C" int stub_last_rehydrate_block_tiles(void) { return t_last_rehydrate.block_tiles; }
+extern "C" int stub_last_rehydrate_token_block(void) { return t_last_rehydrate.token_block; }
 
 extern "C" const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "stub launch error"; }
 

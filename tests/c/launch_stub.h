@@ -9,6 +9,7 @@ long stub_launches(void);                    /* launches so far, all threads */
 int stub_last_rehydrate_row_group(void);     /* this thread's last rehydrate */
 long long stub_last_rehydrate_tasks(void);
 int stub_last_rehydrate_block_tiles(void);   /* 0: persistent schedule */
+int stub_last_rehydrate_token_block(void);   /* per-head kernel */
 #ifdef __cplusplus
 }
 #endif

@@ -432,10 +432,10 @@ def test_shift_matches_oracle(device, name):
 
 @pytest.mark.parametrize("C,L,H,n,m,P", [(2, 1, 1, 1100, 128, 16), (2, 1, 2, 300, 72, 24), (1, 2, 1, 1030, 40, 15),
                                          (3, 2, 3, 130, 64, 17), (2, 2, 1, 70, 16, 64),
-                                         (30, 30, 2, 70, 8, 16)])
+                                         (30, 30, 2, 70, 8, 16), (5, 25, 2, 380, 64, 40), (6, 30, 1, 600, 128, 16)])
 def test_rehydrate_per_head_blocks(device, C, L, H, n, m, P):
-    """The per-head kernel's token blocks and page look-ups: blocks of 64, 128 and
-    256 tokens with a partial last one, pages staged in LDS (16 tokens and more,
+    """The per-head kernel's token blocks and page look-ups: blocks of 64, 128, 192
+    and 320 tokens with a partial last one, pages staged in LDS (16 tokens and more,
     not a power of two, crossing block edges) and looked up one by one (15),
     explicit positions, ragged chunks, both patch frames."""
     import paper_2606_23581_amd as km
