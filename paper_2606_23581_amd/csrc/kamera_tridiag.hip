@@ -1048,11 +1048,13 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
   // ---- 3. the m largest eigenpairs of T ----
   if (wave == 0) {                             // Gershgorin interval and b^2
     float lo = 3.4e38f, hi = -3.4e38f;
+    bool finite = true;
     for (int i = lane; i < d; i += 64) {
       const float bl = i > 0 ? s_b[i - 1] : 0.f, br = i < d - 1 ? s_b[i] : 0.f;
       const float r = fabsf(bl) + fabsf(br);
       lo = fminf(lo, s_a[i] - r);
       hi = fmaxf(hi, s_a[i] + r);
+      finite = finite && fabsf(s_a[i]) + r <= 3.4e38f;
       s_b2[i] = i < d - 1 ? fmaxf(br * br, 1.17549435e-38f) : 0.f;
       s_b2s[i] = i > 0 ? fmaxf(bl * bl, 1.17549435e-38f) : 0.f;
     }
@@ -1060,13 +1062,24 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
       lo = fminf(lo, __shfl_xor(lo, o, 64));
       hi = fmaxf(hi, __shfl_xor(hi, o, 64));
     }
+    const bool ok = __all(finite);
     if (lane == 0) {
       s_misc[0] = lo;
       s_misc[1] = hi;
-      *s_fail = 0;
+      *s_fail = ok && (lo != 0.f || hi != 0.f) ? 0 : 1;
     }
   }
-  __syncthreads();
+  // Leaves the unit to Jacobi (the same on every thread), as soon as it is known:
+  // the vectors of a multiple eigenvalue search the twist once a member, and
+  // eigenvalues that are not numbers, or of T = 0, count as one such (a unit of 64
+  // columns, rank 32, whose T is not finite: 237 us, 80 for an ordinary one).
+  auto failed = [&]() -> bool {
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(*s_fail) == 0) return false;
+    if (tid == 0) P.W[(int64_t)c * P.w_s[0] + (int64_t)l * P.w_s[1] + (int64_t)h * P.w_s[2]] = kFormFailMark;
+    return true;
+  };
+  if (failed()) return;
   const float glo = s_misc[0], ghi = s_misc[1];
   const float tnorm = fmaxf(fabsf(glo), fabsf(ghi));   // |T| bound
   {
@@ -1085,7 +1098,7 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
     else if (m <= 64) multisect<4, 8>(s_as, s_bs, s_lam, s_cnt, s_cs, lo, hi, e, d, m, s_fail);
     else multisect<2, 12>(s_as, s_bs, s_lam, s_cnt, s_cs, lo, hi, e, d, m, s_fail);
   }
-  __syncthreads();
+  if (failed()) return;
   // clusters: runs of eigenvalues within 1e-3 |T| of their predecessor
   // (equal ones always, also when T = 0): s_cs[j] is the last run start at or
   // before j, a running maximum over the starts (wave 0, 64 entries a pass)
@@ -1202,12 +1215,8 @@ __global__ __launch_bounds__(kTriThreads * S, S > 1 ? 2 : 4) void form_tri_kerne
       if (!(r2 <= 0x1p-32f)) *s_fail = 1;
     }
   }
-  __syncthreads();
+  if (failed()) return;
   uint16_t* const Wout = P.W + (int64_t)c * P.w_s[0] + (int64_t)l * P.w_s[1] + (int64_t)h * P.w_s[2];
-  if (*s_fail) {                               // uniform
-    if (tid == 0) Wout[0] = kFormFailMark;
-    return;
-  }
 
   // ---- 4. V_m = Q Z, 64 columns at a time; the blocks' V and T are staged
   // over the columns that are in registers by then (m <= 64), else past them ----

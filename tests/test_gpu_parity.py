@@ -1022,6 +1022,44 @@ def test_form_patch_degenerate_layer(device, C, L, H):
             _check_patch(delta[c, l, h], Ub[c, l, h], Wb[c, l, h], sg[c, l, h], m, (c, l, h))
 
 
+@pytest.mark.parametrize("units,n,d,m", [(9, 70, 128, 64), (9, 70, 64, 1), (288, 40, 128, 16), (300, 33, 32, 32)])
+def test_form_patch_units_without_a_spectrum(device, units, n, d, m):
+    """Units that leave the tridiagonal solver before its vectors -- a deficit that
+    is zero, holds a NaN or an infinity, or whose Gram matrix overflows -- beside
+    ordinary ones: those are as in a call of their own, bit for bit, and a zero
+    deficit gives zero singular values on orthonormal rows."""
+    import paper_2606_23581_amd as km
+    import torch
+
+    print(f"[case] form_patch without a spectrum units {units} n{n} d{d} m{m}", flush=True)
+    rng = np.random.default_rng(n + d)
+    A = np.linalg.qr(rng.standard_normal((units, n, m)))[0]
+    B = np.linalg.qr(rng.standard_normal((units, d, m)))[0]
+    delta = (A * np.linspace(10.0, 2.0, m)) @ np.swapaxes(B, -1, -2) + 0.01 * rng.standard_normal((units, n, d))
+    delta = torch.from_numpy(delta[None, None].astype(np.float32))
+    bad = {1: 0.0, 2: float("nan"), 4: float("inf"), 7: 1e25}
+    mixed = delta.clone()
+    mixed[0, 0, 1] = 0.0
+    mixed[0, 0, 2, n - 1, d - 1] = bad[2]
+    mixed[0, 0, 4, 0, 3] = bad[4]
+    mixed[0, 0, 7] *= bad[7]
+    got = []
+    for x in (delta, mixed):
+        U = torch.zeros((1, 1, units, n, m), dtype=torch.bfloat16, device=device)
+        W = torch.zeros((1, 1, units, m, d), dtype=torch.bfloat16, device=device)
+        sigma = torch.full((1, 1, units, m), -1.0, dtype=torch.float32, device=device)
+        km.form_patch(x.to(device), U, W, sigma=sigma)
+        torch.cuda.synchronize()
+        got.append((bits(U)[0, 0], bits(W)[0, 0], sigma.cpu().numpy()[0, 0]))
+    good = [u for u in range(units) if u not in bad]
+    for a, b in zip(*got):
+        assert np.array_equal(a[good], b[good])
+    for u in (0, units - 1):
+        _check_patch(delta[0, 0, u].numpy(), got[1][0][u], got[1][1][u], got[1][2][u], m, (u,))
+    Wz = ref.bf16_to_f64(got[1][1][1])
+    assert np.array_equal(Wz @ Wz.T, np.eye(m)) and (got[1][0][1] == 0).all() and (got[1][2][1] == 0).all()
+
+
 @pytest.mark.parametrize("K,n,d,m", [(3, 200, 128, 16), (6, 64, 64, 8), (1, 90, 128, 32)])
 def test_orbit_patch_matches_reference(device, K, n, d, m):
     """Orbit patch (Sec. 5, reorder): the K orderings' deficits share a
