@@ -577,12 +577,13 @@ __device__ __forceinline__ void jacobi_unit(const FormParams& P, int unit, int s
   }
   if (P.sweeps_done != nullptr && tid == 0) P.sweeps_done[unit] = sweeps_run;
 
-  // ---- 3. the m largest eigenvalues (ties by index) ----
+  // ---- 3. the m largest eigenvalues (ties by index; NaN counts as the least, so
+  // that every rank is taken) ----
   if (tid < d) {
-    const float li = G[tid * ld + tid];
+    const float li = fmaxf(G[tid * ld + tid], -__builtin_inff());
     int rank = 0;
     for (int j = 0; j < d; ++j) {
-      const float lk = G[j * ld + j];
+      const float lk = fmaxf(G[j * ld + j], -__builtin_inff());
       rank += (lk > li) || (lk == li && j < tid);
     }
     if (rank < m) s_order[rank] = tid;

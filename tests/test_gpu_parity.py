@@ -1056,6 +1056,7 @@ def test_form_patch_units_without_a_spectrum(device, units, n, d, m):
         assert np.array_equal(a[good], b[good])
     for u in (0, units - 1):
         _check_patch(delta[0, 0, u].numpy(), got[1][0][u], got[1][1][u], got[1][2][u], m, (u,))
+    assert (got[1][2][2] >= 0).all()             # every rank names a column, also of NaN
     Wz = ref.bf16_to_f64(got[1][1][1])
     assert np.array_equal(Wz @ Wz.T, np.eye(m)) and (got[1][0][1] == 0).all() and (got[1][2][1] == 0).all()
 
