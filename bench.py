@@ -170,39 +170,47 @@ def jacobi_flops(d: int, sweeps: int) -> int:
 
 
 def tridiagonal_flops(d: int, m: int) -> int:
-    """Tridiagonal-solver flops on one unit, as the kernel executes them:
-    Householder steps on the full trailing block of order L = d-1-j (the
-    product A v, 2 L^2, and the rank-2 update, 4 L^2, plus 3 L for the
-    reflector and w), 8 multisection rounds of 8 Sturm sequences per
-    eigenvalue (4 flops per pivot), the twisted factorisation's four passes
-    (D-, D+ beside the twist search, D+ above the twist, the vector and its
-    norm: ~4 flops per element each), and the back-transformation (a dot
-    product and an update of 2 L flops each per reflector and vector)."""
-    house = sum(6 * L * L + 3 * L for L in range(2, d))
-    bisect = 8 * 8 * 4 * d * m
+    """Tridiagonal-solver flops on one unit, as the kernel executes them (d padded
+    to blocks of 32 where it works on tiles): Householder steps on the full
+    trailing block of order L = d-1-j (the product A v, 2 L^2, the rank-2 update,
+    4 L^2, and 5 L for the reflector and w); Sturm sequences at 256 points and at
+    `lanes` points a round and eigenvalue (4 flops a row); the twisted
+    factorisation's four passes (~4 flops a row each); per block of 32 reflectors
+    the compact WY form (V^T V, 2 * 32^2 L, and T, 32^3 / 3) and its product with
+    the m vectors, padded to 16 (V^T Z and V Y, 2 * 32 L each, T C, 2 * 32^2)."""
+    lanes, rounds = (8, 6) if m <= 32 else (4, 8) if m <= 64 else (2, 12)
+    dp, mp = (d + 31) // 32 * 32, (m + 15) // 16 * 16
+    house = sum(6 * L * L + 5 * L for L in range(2, d))
+    bisect = (256 + lanes * rounds * m) * 4 * d
     vectors = 4 * 4 * d * m
-    back = sum(4 * L * m for L in range(2, d))
+    back = sum(2 * 32 * 32 * L + 32 ** 3 // 3 + (4 * 32 * L + 2 * 32 * 32) * mp for L in range(dp, 0, -32))
     return house + bisect + vectors + back
 
 
 def form_flops(n: int, d: int, m: int, sweeps: int, orbit: int = 1) -> int:
-    """Flops of the patch-forming kernel on one unit: the Gram matrix on the
-    upper-triangle 16x16 tiles (padded), the eigensolver -- the tridiagonal
-    one when `sweeps` is 0, else `sweeps` block-Jacobi sweeps -- and
-    U = Delta V_m (padded)."""
+    """Flops of the patch-forming kernels on one unit, fp32 products counted once
+    (the Gram matrix takes each as six bf16 ones): the Gram matrix -- all 32x32
+    tiles in the tridiagonal solver, which is meant when `sweeps` is 0, the
+    upper-triangle 16x16 tiles before `sweeps` sweeps of block Jacobi -- the
+    eigensolver, and U = Delta V_m (padded).  A unit that the solver left to
+    Jacobi counts as the latter alone."""
     dp = (d + 15) // 16 * 16
     mp = (m + 15) // 16 * 16
     nt = dp // 16
-    gram = n * 512 * nt * (nt + 1) // 2
-    eig = tridiagonal_flops(d, m) if sweeps == 0 else jacobi_flops(d, sweeps)
+    if sweeps == 0:
+        dt = (d + 31) // 32 * 32
+        eig = 2 * n * dt * dt + tridiagonal_flops(d, m)
+    else:
+        eig = n * 512 * nt * (nt + 1) // 2 + jacobi_flops(d, sweeps)
     mean = 0 if orbit <= 1 else 2 * orbit * n * d          # orbit mean, formed in both passes over Delta
-    return gram + eig + 2 * n * dp * mp + mean
+    return eig + 2 * n * dp * mp + mean
 
 
 def bench_form(args, pool, n_workers):
     """One step = forming the K and the V patches of every (chunk, layer, head)
-    unit of the workload from fp32 deficits (one launch per plane), with the
-    tridiagonal eigensolver (--sweeps 0, the default) or block Jacobi."""
+    unit of the workload from fp32 deficits (one call per plane: the tridiagonal
+    solver, Jacobi for the units that it left, and U -- or, with --sweeps, block
+    Jacobi and U)."""
     import numpy as np
     import torch
 
@@ -299,7 +307,8 @@ def bench_form(args, pool, n_workers):
         "sweeps_run": {"min": int(sw.min()), "mean": round(float(sw.mean()), 2), "max": int(sw.max())},
         "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": FP32_MATRIX_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / FP32_MATRIX_PEAK_TFLOPS, 4), "traffic": None,
-                     "kernel": "form_patch_kernel + form_u_kernel", "kernel_ms": round(gpu_ms / len(planes), 4),
+                     "kernel": ("form_tri_kernel + form_patch_kernel + form_u_kernel" if args.sweeps == 0
+                                else "form_patch_kernel + form_u_kernel"), "kernel_ms": round(gpu_ms / len(planes), 4),
                      "flops_per_step": int(flops)},
         "cpu_baseline": cpu,
     }
