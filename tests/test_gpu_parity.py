@@ -780,9 +780,11 @@ def test_form_patch_row_strides(device, n, d, m, wide):
 @pytest.mark.parametrize("units", [96, 288])
 def test_form_patch_zero_leading_entry(device, units):
     """Deficits whose reflector of column `deep` starts from an entry that is zero
-    but for rounding: the sign that the reduction's step took for it has to be
-    the one that the back-transformation uses (the matrix is no longer symmetric
-    to the bit by then, so the row and the column may differ in it)."""
+    but for rounding, whose sign the matrix's row and column may not share: the
+    back-transformation has to take the reflector of the step.  |x| stays far
+    above rounding here, so it is the choice of the sign that is tried, on many
+    units; a row that is rounding alone, where the two are other vectors, is in
+    test_form_patch_weakly_coupled_channel."""
     import paper_2606_23581_amd as km
     import torch
 
