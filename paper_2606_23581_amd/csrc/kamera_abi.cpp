@@ -230,22 +230,22 @@ static int pick_token_block(int64_t units, int32_t n_tokens, int m_steps, bool r
   if (m_steps > 2) m_steps = 4;                // as the kernel is instantiated
   const double setup = 0.4 * std::max(m_steps, 1);
   const double places = 256.0 * (m_steps > 2 || relocated ? 3 : 4);   // its launch bounds
-  const int64_t passes = ceil_div(n_tokens, 64);
-  int64_t best = 1;
+  const double full = (double)units / places;
+  const int32_t passes = (n_tokens - 1) / 64 + 1;
+  int32_t best = 1;
   double least = 0.0;
-  for (int64_t most = kamera::kMaxTokenBlock / 64; most >= 1; --most) {
-    if (m_steps <= 1 && (most & (most - 1)) != 0) continue;
-    int64_t len = std::min(most, passes);
-    if (m_steps > 1) len = ceil_div(passes, ceil_div(passes, len));
-    const double blocks = (double)ceil_div(passes, len), one = setup + std::min((double)len, n_tokens / 64.0);
-    const double sum = (double)units * (blocks * setup + (double)passes) / places;
-    const double cost = (double)units * blocks <= places ? std::max(sum, one) + 0.5 * one : sum + 1.1 * one;
+  for (int32_t most = std::min(passes, kamera::kMaxTokenBlock / 64); most >= 1; --most) {
+    if (m_steps <= 1 && most < passes && (most & (most - 1)) != 0) continue;
+    const int32_t blocks = (passes + most - 1) / most, len = m_steps > 1 ? (passes + blocks - 1) / blocks : most;
+    const double one = setup + std::min((double)len, n_tokens / 64.0);
+    const double sum = full * (blocks * setup + passes);
+    const double cost = full * blocks <= 1.0 ? std::max(sum, one) + 0.5 * one : sum + 1.1 * one;
     if (least == 0.0 || cost < least) {
       least = cost;
       best = len;
     }
   }
-  return (int)(64 * best);
+  return 64 * best;
 }
 
 static int build_rehydrate(const kamera_rehydrate_args* a, kamera::RehydrateParams& P, bool& launch) {
